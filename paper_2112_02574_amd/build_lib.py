@@ -17,12 +17,17 @@ LIB = os.path.join(HERE, "libscmc.so")
 # once per storage format and stencil order so that they compile in parallel
 SOURCES = [("step_kernels.hip", "step_kernels", []),
            ("fused_kernels.hip", "fused_kernels", []),
+           ("moment_kernels.hip", "moment_kernels", []),
            ("obs_kernels.hip", "obs_kernels", []),
            ("ceiling_kernels.hip", "ceiling_kernels", []),
            ("scmc_api.cpp", "scmc_api", [])]
 for _st in ("StoreF32", "StoreF16", "StoreBF16"):
     for _order in (4, 6):
         SOURCES.append(("fused_inst.hip", f"fused_{_st}_{_order}",
+                        [f"-DSCMC_INST_STORE=scmc::{_st}", f"-DSCMC_INST_ORDER={_order}"]))
+for _st in ("StoreF64", "StoreF32", "StoreF16", "StoreBF16"):
+    for _order in (4, 6):
+        SOURCES.append(("moment_inst.hip", f"moment_{_st}_{_order}",
                         [f"-DSCMC_INST_STORE=scmc::{_st}", f"-DSCMC_INST_ORDER={_order}"]))
 ARCH = os.environ.get("SCMC_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

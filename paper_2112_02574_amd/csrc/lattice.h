@@ -142,6 +142,7 @@ struct StoreF64 {
     static constexpr int BYTES = 8;
     __device__ __forceinline__ static R from_raw(T v, R) { return v; }
     __device__ __forceinline__ static T to_raw(R v, R) { return v; }
+    __device__ __forceinline__ static R stored(R v, R, R) { return v; }
     __device__ __forceinline__ static R load(const T *p, long i, R) { return p[i]; }
     __device__ __forceinline__ static void store(T *p, long i, R v, R) {
         __builtin_nontemporal_store(v, p + i);
@@ -155,6 +156,7 @@ struct StoreF32 {
     static constexpr int BYTES = 4;
     __device__ __forceinline__ static R from_raw(T v, R) { return v; }
     __device__ __forceinline__ static T to_raw(R v, R) { return v; }
+    __device__ __forceinline__ static R stored(R v, R, R) { return v; }
     __device__ __forceinline__ static R load(const T *p, long i, R) { return p[i]; }
     __device__ __forceinline__ static void store(T *p, long i, R v, R) {
         __builtin_nontemporal_store(v, p + i);
@@ -178,6 +180,13 @@ struct StoreF16 {
     __device__ __forceinline__ static void store(T *p, long i, R v, R ref) {
         const T h = __half_as_ushort(__float2half_rn(v - ref));
         __builtin_nontemporal_store(h, p + i);
+    }
+    // The value that a load finds of a stored one, with the reference w n0
+    // inside both roundings, as the compiler contracts to_raw and from_raw
+    // around the product in the two passes.
+    __device__ __forceinline__ static R stored(R v, R w, R n0) {
+        const T h = __half_as_ushort(__float2half_rn(__builtin_fmaf(-w, n0, v)));
+        return __builtin_fmaf(w, n0, __half2float(__ushort_as_half(h)));
     }
     // Node storage (offsets from the node's own rest equilibrium, which are
     // small where the flow is slow): the offset is scaled by 2^10 before it
@@ -242,6 +251,9 @@ struct StoreBF16 {
     __device__ __forceinline__ static void store(T *p, long i, R v, R ref) {
         const T h = f32_to_bf16_dev(v - ref);
         __builtin_nontemporal_store(h, p + i);
+    }
+    __device__ __forceinline__ static R stored(R v, R w, R n0) {  // as StoreF16::stored
+        return __builtin_fmaf(w, n0, bf16_to_f32(f32_to_bf16_dev(__builtin_fmaf(-w, n0, v))));
     }
     // node storage: bfloat16 has the binary32 exponent range, no scale
     __device__ __forceinline__ static T to_node(R v, R ref) { return to_raw(v, ref); }

@@ -207,6 +207,9 @@ struct Common {
 struct scmc_sim {
     Common c;
     Lat lat;
+    bool mom_ok = false;  // blocks of steps can stay in the moment field
+    NodeLaunch mom_node{};
+    MomShape mom_shape{};
     bool have_prev = false;  // convergence monitor: a previous check exists
     double prev_dP = 0;
     int64_t prev_step = 0;
@@ -860,6 +863,68 @@ int direct_step_sim(scmc_sim *s) {
     return SCMC_OK;
 }
 
+// Whether a block of steps of this handle runs on the moment field alone.
+bool mom_steps_on(const scmc_sim *s) {
+    return s->mom_ok && s->c.kernel == SCMC_KERNEL_TWO_PASS && s->c.key.mom && !s->c.key.sr;
+}
+
+// The launches of k >= 2 steps from buffer par that stay in the moment field:
+// pass 1, k - 1 moment steps, pass 2; each goes to emit(launch, arguments).
+// The moments alternate between the workspace's moment field, where the last
+// ones must be for pass 2, and the population buffer that pass 1 does not
+// read, whose contents no one needs any more and pass 2 at most overwrites
+// (24 or 48 B per site of its 76 to 304).  Node storage keeps the last pairs
+// as the reference field of the buffer that pass 2 fills.
+template <class Emit>
+int mom_steps(scmc_sim *s, int64_t k, int par, Emit &&emit) {
+    Common &c = s->c;
+    const Member &m = s->lat.m;
+    const int last = par ^ (int)((k - 1) & 1);
+    NodeLaunch p1{}, p2{};
+    if (!node_two_pass(c.key, &p1, &p2, m))
+        return fail(c, SCMC_EUNSUPPORTED, "no two-pass kernel for this problem");
+    p1.grid = dim3(linear_blocks(m, m.nz, (int)p1.block.x));
+    if (c.key.mom == 1) p2.grid = dim3(linear_blocks(m, m.nz, (int)p2.block.x));
+    Member m1 = step_member(c, m, par), m2 = step_member(c, m, last);
+    void *field[2] = {c.dens, c.pop[1 - par]};
+    const int slot[2] = {m2.pair_slot, 0};
+    int at = (int)((k - 1) & 1);  // the field that holds the current moments
+    m1.pair_slot = slot[at];
+    const void *src = c.pop[par], *src2 = c.pop[last];
+    void *dst = c.pop[1 - last];
+    std::vector<void *> a1 = {(void *)&m1, (void *)&src, (void *)&field[at]};
+    int rc = emit(p1, a1);
+    Member ms = m;
+    MomShape shape = s->mom_shape;
+    for (int64_t t = 1; t < k && !rc; ++t, at ^= 1) {
+        int si = slot[at], so = slot[1 - at];
+        std::vector<void *> a = {(void *)&ms, (void *)&shape, (void *)&field[at],
+                                 (void *)&field[1 - at], (void *)&si, (void *)&so};
+        rc = emit(s->mom_node, a);
+    }
+    std::vector<void *> a2 = {(void *)&m2, (void *)&src2, (void *)&dst, (void *)&field[0]};
+    return rc ? rc : emit(p2, a2);
+}
+
+// k steps of a single lattice outside graphs.
+int direct_steps_sim(scmc_sim *s, int64_t k) {
+    Common &c = s->c;
+    if (k < 2 || !mom_steps_on(s)) {
+        int rc = SCMC_OK;
+        for (int64_t t = 0; t < k && !rc; ++t) rc = direct_step_sim(s);
+        return rc;
+    }
+    const int rc = mom_steps(s, k, c.cur, [&](const NodeLaunch &nl, std::vector<void *> &args) {
+        const hipError_t e =
+            hipLaunchKernel(nl.func, nl.grid, nl.block, args.data(), nl.shmem, c.stream);
+        return e == hipSuccess
+                   ? SCMC_OK
+                   : fail(c, SCMC_EDEVICE, "step launch: %s", hipGetErrorString(e));
+    });
+    if (!rc && (k & 1)) c.cur ^= 1;
+    return rc;
+}
+
 hipError_t launch_op(scmc_batch *b, const BatchOp &o, const void *src, void *dst) {
     const Common &c = b->c;
     return o.member >= 0 ? launch_member_pass(c.key, o.m, src, dst, c.dens, o.pass, o.nt_all,
@@ -934,7 +999,7 @@ struct ArgPack {
 int build_graph(Common &c, int k, int par, bool batch, const Member &m,
                 const Member *d_members, const Tile *d_tiles,
                 const std::vector<int> &chunks, int grid,
-                const std::vector<BatchOp> *ops = nullptr) {
+                const std::vector<BatchOp> *ops = nullptr, scmc_sim *sim = nullptr) {
     hipGraph_t g = nullptr;
     HIPCHK(c, hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
@@ -995,7 +1060,9 @@ int build_graph(Common &c, int k, int par, bool batch, const Member &m,
                 }
             }
     }
-    for (int t = 0; !ops && t < k && !rc; ++t) {
+    const bool mom = sim && k >= 2 && mom_steps_on(sim);
+    if (mom) rc = mom_steps(sim, k, par, add);
+    for (int t = 0; !ops && !mom && t < k && !rc; ++t) {
         for (size_t ch = 0; ch + 1 < chunks.size() && !rc; ++ch) {
             const int ntiles = chunks[ch + 1] - chunks[ch];
             // persistent fused launches: at most `grid` workgroups (clamped to
@@ -1085,12 +1152,11 @@ int build_graph(Common &c, int k, int par, bool batch, const Member &m,
     return SCMC_OK;
 }
 
-// Steps outside graphs go one at a time through direct(), or, where many is
-// given, in blocks of up to kStepBlock steps through many(k).
+// Steps outside graphs go in blocks of up to kStepBlock steps through many(k).
 constexpr int64_t kStepBlock = 64;
 
-template <class StepFn, class BuildFn, class ManyFn = std::nullptr_t>
-int run_steps(Common &c, int64_t nsteps, StepFn direct, BuildFn build, ManyFn many = nullptr) {
+template <class BuildFn, class ManyFn>
+int run_steps(Common &c, int64_t nsteps, BuildFn build, ManyFn many) {
     if (nsteps < 0) return fail(c, SCMC_EINVAL, "nsteps < 0");
     if (!c.initialized)
         return fail(c, SCMC_ESTATE, "state not set (call set_density first)");
@@ -1105,17 +1171,12 @@ int run_steps(Common &c, int64_t nsteps, StepFn direct, BuildFn build, ManyFn ma
             if (c.graph_k % 2) c.cur ^= 1;
             left -= c.graph_k;
             c.step += c.graph_k;
-        } else if constexpr (!std::is_same<ManyFn, std::nullptr_t>::value) {
+        } else {
             const int64_t k = std::min(left, kStepBlock);
             int rc = many(k);
             if (rc) return rc;
             left -= k;
             c.step += k;
-        } else {
-            int rc = direct();
-            if (rc) return rc;
-            --left;
-            ++c.step;
         }
     }
     return SCMC_OK;
@@ -1184,6 +1245,7 @@ int scmc_create(const scmc_problem *p, void *d_ws, size_t ws_bytes,
     c.ws_bytes = ws_bytes;
     bind(c, pl, c.ws, stats_blocks(s->lat.m));
     s->lat.m.step_ctr = c.ctr;
+    s->mom_ok = node_mom_step(c.key, s->lat.m, &s->mom_node, &s->mom_shape);
     *out = s;
     return SCMC_OK;
 }
@@ -1246,12 +1308,13 @@ int scmc_step(scmc_sim *s, int64_t nsteps) {
     if (!s) return SCMC_EINVAL;
     Common &c = s->c;
     return run_steps(
-        c, nsteps, [&] { return direct_step_sim(s); },
+        c, nsteps,
         [&](int par) {
             static const std::vector<int> whole = {0, 0};
             return build_graph(c, c.graph_k, par, false, s->lat.m, nullptr,
-                               nullptr, whole, 0);
-        });
+                               nullptr, whole, 0, nullptr, s);
+        },
+        [&](int64_t k) { return direct_steps_sim(s, k); });
 }
 
 // ---- the allocation-free step ----------------------------------------------
@@ -1871,7 +1934,7 @@ int scmc_batch_step(scmc_batch *b, int64_t nsteps) {
     if (!b) return SCMC_EINVAL;
     Common &c = b->c;
     return run_steps(
-        c, nsteps, [&] { return direct_step_batch(b); },
+        c, nsteps,
         [&](int par) {
             const std::vector<int> whole = {0, b->ntiles};
             return build_graph(c, c.graph_k, par, true, Member{}, b->d_members, b->d_tiles,
@@ -2040,17 +2103,17 @@ void cache_store(const char *path, const std::string &key, const Candidate &c,
     fclose(f);
 }
 
-// Time `steps` launches of step() on the handle's stream, in microseconds.
+// Time a call of `steps` steps, step(n), on the handle's stream, in
+// microseconds per step.
 template <class StepFn>
 int time_steps(Common &c, int warm, int steps, StepFn step, double *us) {
     hipEvent_t e0, e1;
     HIPCHK(c, hipEventCreate(&e0));
     HIPCHK(c, hipEventCreate(&e1));
-    int rc = SCMC_OK;
-    for (int i = 0; i < warm && !rc; ++i) rc = step();
+    int rc = step(warm);
     if (!rc) {
         (void)hipEventRecord(e0, c.stream);
-        for (int i = 0; i < steps && !rc; ++i) rc = step();
+        rc = step(steps);
         (void)hipEventRecord(e1, c.stream);
         (void)hipEventSynchronize(e1);
         float ms = 0;
@@ -2101,7 +2164,7 @@ int scmc_autotune(scmc_sim *s, const char *cache_path, int *tile) {
             for (size_t i = 0; i < cands.size(); ++i) {
                 apply(c, cands[i]);
                 double us = 0;
-                rc = time_steps(c, 4, 20, [&] { return direct_step_sim(s); }, &us);
+                rc = time_steps(c, 4, 20, [&](int k) { return direct_steps_sim(s, k); }, &us);
                 if (rc) return rc;
                 t[i] = std::min(t[i], us);
             }
@@ -2164,7 +2227,7 @@ int scmc_batch_autotune(scmc_batch *b, const char *cache_path, int *tile) {
             if (rc == SCMC_ENOSPACE) continue;
             if (rc) return rc;
             double us = 0;
-            rc = time_steps(c, 1, 4, [&] { return direct_step_batch(b); }, &us);
+            rc = time_steps(c, 1, 4, [&](int k) { return direct_steps_batch(b, k); }, &us);
             if (rc) return rc;
             if (us < best_us) {
                 best_us = us;

@@ -140,6 +140,18 @@ bool node_batch_two_pass(const StepKey &k, int grid, NodeLaunch *dens_node,
 bool node_batch_fused(const StepKey &k, const int *tile, int grid,
                       NodeLaunch *node);
 
+// ---- steps that stay in the moment field (moment_impl.h; D3Q19, tau = 1)
+constexpr int MOM_THREADS = 1024;          // two lanes per node, one per component
+constexpr int MOM_EXT = MOM_THREADS / 2;   // nodes of a column's plane with its rim
+// Columns of w x h nodes (ntx x nty of them) in chunks of zc planes.
+struct MomShape {
+    int w, h, zc, ntx, nty, nchunks;
+};
+// The kernel of one such step of m and its launch shape; false: none for this
+// key.  Kernel arguments: Member, MomShape, const void *in, void *out (moment
+// fields), int in_slot, int out_slot (slots of their (n_A, n_B) pairs).
+bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape);
+
 // ---- bandwidth ceiling (ceiling_kernels.hip): the 2Q population planes of
 // src copied to dst with the pull shifts, one site per lane; elements of
 // `bytes` bytes (8, 4 or 2)

@@ -10,6 +10,8 @@
 //             S_i  = w_i [3 xi.F + 9 (xi.u)(xi.F) - 3 u.F]     (c_s^2 = 1/3)
 #pragma once
 
+#include <type_traits>
+
 #include "lattice.h"
 #include "scmc_internal.h"
 
@@ -274,28 +276,96 @@ __device__ __forceinline__ void site_collide(const Member &m,
 // exactly instead of re-rounding the same sum the same way every step.
 constexpr int NMOM = 7;  // n_A, n_B, j_x, j_y, j_z, rem(n_A), rem(n_B)
 
+// Raw moments of one component's populations, FP64: n = sum_i f_i and
+// j = sum_i xi_i f_i, summed in groups of equal xi_z (+1, 0, -1), each in the
+// order of i: a march through the z-planes that receives the populations of
+// plane z - 1 first, then those of plane z and of plane z + 1 forms the same
+// sums, also where they round (FP64 storage).
+template <class R>
+__device__ __forceinline__ void add_group(int cz, const R (&f)[19], double &g, double &jx,
+                                          double &jy) {
+    using L = Lattice<3>;
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        if (L::CZ[i] != cz) continue;
+        g += (double)f[i];
+        if (L::CX[i]) jx += (double)L::CX[i] * (double)f[i];
+        if (L::CY[i]) jy += (double)L::CY[i] * (double)f[i];
+    }
+}
+
+template <int D, class R>
+__device__ __forceinline__ void raw_moments(const R (&f)[Lattice<D>::Q], double &n, double &jx,
+                                            double &jy, double &jz) {
+    using L = Lattice<D>;
+    jx = jy = jz = 0;
+    if constexpr (D == 3) {
+        double gp = 0, g0 = 0, gm = 0;
+        add_group(1, f, gp, jx, jy);
+        add_group(0, f, g0, jx, jy);
+        add_group(-1, f, gm, jx, jy);
+        n = (gp + g0) + gm;
+        jz = gp - gm;
+    } else {
+        n = 0;
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) {
+            n += (double)f[i];
+            if (L::CX[i]) jx += (double)L::CX[i] * (double)f[i];
+            if (L::CY[i]) jy += (double)L::CY[i] * (double)f[i];
+        }
+    }
+}
+
 template <int D, class R>
 __device__ __forceinline__ void site_moments(const R (&f)[2][Lattice<D>::Q],
                                              R (&mom)[NMOM]) {
-    using L = Lattice<D>;
-    double nA = 0, nB = 0;
-    double jx = 0, jy = 0, jz = 0;  // order-free sums (see site_density)
+    double n[2], jx[2], jy[2], jz[2];  // order-free sums (see site_density)
 #pragma unroll
-    for (int i = 0; i < L::Q; ++i) {
-        nA += (double)f[0][i];
-        nB += (double)f[1][i];
-        const double t = (double)f[0][i] + (double)f[1][i];
-        if (L::CX[i]) jx += (double)L::CX[i] * t;
-        if (L::CY[i]) jy += (double)L::CY[i] * t;
-        if (D == 3 && L::CZ[i]) jz += (double)L::CZ[i] * t;
+    for (int J = 0; J < 2; ++J) raw_moments<D, R>(f[J], n[J], jx[J], jy[J], jz[J]);
+    mom[0] = (R)n[0];
+    mom[1] = (R)n[1];
+    mom[2] = (R)(jx[0] + jx[1]);
+    mom[3] = (R)(jy[0] + jy[1]);
+    mom[4] = (R)(jz[0] + jz[1]);
+    mom[5] = (R)(n[0] - (double)mom[0]);
+    mom[6] = (R)(n[1] - (double)mom[1]);
+}
+
+// The FP64 remainders of n_A, n_B (at most half an ulp of the stored value)
+// travel as two halves of one 32-bit word, in units of that ulp: 11 bits of
+// the remainder keep the rest population's mass closure exact to 2^-12 ulp,
+// far inside its own rounding.  FP64 compute has no remainder.
+__device__ __forceinline__ unsigned pack_rem1(float n, float rem) {
+    int e;
+    frexpf(n, &e);
+    const float q = ldexpf(rem, 24 - e);  // remainder / ulp(n_J)
+    return (unsigned)__half_as_ushort(__float2half_rn(q));
+}
+
+__device__ __forceinline__ float unpack_rem1(unsigned h, float n) {
+    int e;
+    frexpf(n, &e);
+    const float q = __half2float(__ushort_as_half((unsigned short)h));
+    return ldexpf(q, e - 24);
+}
+
+template <class R>
+__device__ __forceinline__ unsigned pack_rem(const R (&mm)[NMOM]) {
+    if constexpr (std::is_same<R, double>::value)
+        return 0u;
+    else
+        return pack_rem1(mm[0], mm[5]) | pack_rem1(mm[1], mm[6]) << 16;
+}
+
+template <class R>
+__device__ __forceinline__ void unpack_rem(unsigned w, R (&mm)[NMOM]) {
+    if constexpr (std::is_same<R, double>::value) {
+        mm[5] = mm[6] = 0;
+    } else {
+        mm[5] = unpack_rem1(w, mm[0]);
+        mm[6] = unpack_rem1(w >> 16, mm[1]);
     }
-    mom[0] = (R)nA;
-    mom[1] = (R)nB;
-    mom[2] = (R)jx;
-    mom[3] = (R)jy;
-    mom[4] = (R)jz;
-    mom[5] = (R)(nA - (double)mom[0]);
-    mom[6] = (R)(nB - (double)mom[1]);
 }
 
 // The collision at omega = 1 (tau = 1), where f* = f^eq(n_J, u) + S_i / 2
@@ -311,41 +381,44 @@ __device__ __forceinline__ void site_moments(const R (&f)[2][Lattice<D>::Q],
 // 1) and re-rounded sums would otherwise bias the mass by the same relative
 // amount every step.
 template <int D, class R, class Emit>
+__device__ __forceinline__ void collide_tau1_component(R nJ, R remJ, const R (&F)[3], R ux, R uy,
+                                                       R uz, Emit &&emit) {
+    using L = Lattice<D>;
+    constexpr Opposite<D> OP = Opposite<D>::make();
+    const R uu = ux * ux + uy * uy + uz * uz;
+    const R uF = ux * F[0] + uy * F[1] + uz * F[2];
+    const R a = nJ * (R(1) - R(1.5) * uu) - R(1.5) * uF;
+    double moving = 0;
+#pragma unroll
+    for (int i = 1; i < L::Q; ++i) {
+        const int ib = OP.opp[i];
+        if (ib < i) continue;
+        R xu = 0, xF = 0;
+        if (L::CX[i]) { xu += (R)L::CX[i] * ux; xF += (R)L::CX[i] * F[0]; }
+        if (L::CY[i]) { xu += (R)L::CY[i] * uy; xF += (R)L::CY[i] * F[1]; }
+        if (D == 3 && L::CZ[i]) { xu += (R)L::CZ[i] * uz; xF += (R)L::CZ[i] * F[2]; }
+        const R w = (R)L::W[i];
+        const R t = nJ * xu;
+        const R E = w * (a + R(4.5) * xu * (t + xF));
+        const R O = w * (R(3) * t + R(1.5) * xF);
+        const R fp = emit(i, E + O), fm = emit(ib, E - O);
+        moving += (double)fp + (double)fm;
+    }
+    const double nJx = (double)nJ + (double)remJ;
+    emit(0, (R)(nJx - moving));
+}
+
+template <int D, class R, class Emit>
 __device__ __forceinline__ void collide_tau1_emit(const R (&mom)[NMOM], const R (&FA)[3],
                                                   const R (&FB)[3], Emit &&emit) {
-    using L = Lattice<D>;
-    const R nA = mom[0], nB = mom[1];
-    const R inv = R(1) / (nA + nB);
+    const R inv = R(1) / (mom[0] + mom[1]);
     const R ux = (mom[2] + R(0.5) * (FA[0] + FB[0])) * inv;
     const R uy = (mom[3] + R(0.5) * (FA[1] + FB[1])) * inv;
     const R uz = D == 3 ? (mom[4] + R(0.5) * (FA[2] + FB[2])) * inv : R(0);
-    const R uu = ux * ux + uy * uy + uz * uz;
-    constexpr Opposite<D> OP = Opposite<D>::make();
 #pragma unroll
-    for (int J = 0; J < 2; ++J) {
-        const R *F = J == 0 ? FA : FB;
-        const R nJ = J == 0 ? nA : nB;
-        const R uF = ux * F[0] + uy * F[1] + uz * F[2];
-        const R a = nJ * (R(1) - R(1.5) * uu) - R(1.5) * uF;
-        double moving = 0;
-#pragma unroll
-        for (int i = 1; i < L::Q; ++i) {
-            const int ib = OP.opp[i];
-            if (ib < i) continue;
-            R xu = 0, xF = 0;
-            if (L::CX[i]) { xu += (R)L::CX[i] * ux; xF += (R)L::CX[i] * F[0]; }
-            if (L::CY[i]) { xu += (R)L::CY[i] * uy; xF += (R)L::CY[i] * F[1]; }
-            if (D == 3 && L::CZ[i]) { xu += (R)L::CZ[i] * uz; xF += (R)L::CZ[i] * F[2]; }
-            const R w = (R)L::W[i];
-            const R t = nJ * xu;
-            const R E = w * (a + R(4.5) * xu * (t + xF));
-            const R O = w * (R(3) * t + R(1.5) * xF);
-            const R fp = emit(J, i, E + O), fm = emit(J, ib, E - O);
-            moving += (double)fp + (double)fm;
-        }
-        const double nJx = (double)nJ + (double)mom[5 + J];
-        emit(J, 0, (R)(nJx - moving));
-    }
+    for (int J = 0; J < 2; ++J)
+        collide_tau1_component<D, R>(mom[J], mom[5 + J], J == 0 ? FA : FB, ux, uy, uz,
+                                     [&](int i, R v) { return emit(J, i, v); });
 }
 
 // The same with every f*_i^J handed to sink(J, i, value, w_i n0_J), the

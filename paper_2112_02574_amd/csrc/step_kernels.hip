@@ -108,42 +108,6 @@ __global__ void __launch_bounds__(256)
 template <class R> using Pair = typename std::conditional<std::is_same<R, float>::value,
                                                           float2, double2>::type;
 
-// The FP64 remainders of n_A, n_B (at most half an ulp of the stored value)
-// travel as two halves of one 32-bit word, in units of that ulp: 11 bits of
-// the remainder keep the rest population's mass closure exact to 2^-12 ulp,
-// far inside its own rounding.  FP64 compute has no remainder.
-template <class R>
-__device__ __forceinline__ unsigned pack_rem(const R (&mm)[NMOM]) {
-    if constexpr (std::is_same<R, double>::value) {
-        return 0u;
-    } else {
-        unsigned out = 0;
-#pragma unroll
-        for (int J = 0; J < 2; ++J) {
-            int e;
-            frexpf(mm[J], &e);
-            const float q = ldexpf(mm[5 + J], 24 - e);  // remainder / ulp(n_J)
-            out |= (unsigned)__half_as_ushort(__float2half_rn(q)) << (16 * J);
-        }
-        return out;
-    }
-}
-
-template <class R>
-__device__ __forceinline__ void unpack_rem(unsigned w, R (&mm)[NMOM]) {
-    if constexpr (std::is_same<R, double>::value) {
-        mm[5] = mm[6] = 0;
-    } else {
-#pragma unroll
-        for (int J = 0; J < 2; ++J) {
-            int e;
-            frexpf(mm[J], &e);
-            const float q = __half2float(__ushort_as_half((unsigned short)(w >> (16 * J))));
-            mm[5 + J] = ldexpf(q, e - 24);
-        }
-    }
-}
-
 // moment field of a member: (n_A, n_B) pairs [z][y][x], then the planes j_x,
 // j_y (, j_z), then the packed remainders of n_A and n_B (plane 5)
 template <int D, class ST>

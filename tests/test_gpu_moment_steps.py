@@ -1,0 +1,83 @@
+"""Blocks of steps on the moment field (D3Q19, tau = 1) against single steps.
+
+A call of k >= 2 steps reads the populations once, stays in the moment field
+for k - 1 steps and stores populations once; a call of one step runs pass 1
+and pass 2, which the other tests check against the oracle.  Both form every
+population and every sum from the same operations in the same order, so their
+populations are equal bit for bit: the tolerance is zero.
+"""
+import numpy as np
+import pytest
+
+from paper_2112_02574_amd import inputs, scmc
+
+pytestmark = pytest.mark.gpu
+
+ASYM = ((-0.2, 1.8), (1.8, 0.0))
+PAPER = ((-1.478, 0.5), (0.5, -1.2))
+
+
+def _problem(shape, stencil, storage, psi=scmc.PSI_N, g=ASYM):
+    return scmc.problem(scmc.D3Q19, stencil, shape, g=g, psi_self=psi, storage=storage)
+
+
+def _state(shape, seed=5):
+    nz, ny, nx = shape
+    nA, nB = inputs.droplet(nx, ny, nz, R=max(2.0, min(shape) / 4))
+    n = nA.size
+    noise = [1 + 1e-3 * (2 * inputs.splitmix64_uniform_array(seed + t, n) - 1).reshape(nA.shape)
+             for t in range(2)]
+    return nA * noise[0], nB * noise[1]
+
+
+def _run(p, state, calls, graph=0):
+    s = scmc.Sim(p)
+    s.scmc_set_density(*state)
+    if graph:
+        s.scmc_set_graph_steps(graph)
+    for k in calls:
+        s.scmc_step(k)
+    f = s.scmc_get_populations()
+    n = s.scmc_get_fields()
+    s.close()
+    return f[0] if isinstance(f, tuple) else f, n
+
+
+# smallest extents, one column, several columns with remainders in x, y and z,
+# rows longer than a column's plane holds
+SHAPES = {4: [(3, 3, 3), (4, 7, 5), (9, 33, 67), (5, 3, 300), (40, 5, 8)],
+          6: [(5, 5, 5), (6, 9, 7), (19, 35, 66), (7, 5, 261), (33, 21, 20)]}
+STORAGES = [scmc.F64, scmc.F32, scmc.F16_OFF, scmc.BF16_OFF, scmc.F16_NODE, scmc.BF16_NODE]
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("stencil", [4, 6])
+@pytest.mark.parametrize("psi,g", [(scmc.PSI_N, ASYM), (scmc.PSI_EXP_NEG_INV, PAPER)])
+def test_block_equals_single_steps(storage, stencil, psi, g):
+    for shape in SHAPES[stencil]:
+        p, st = _problem(shape, stencil, storage, psi, g), _state(shape)
+        f1, n1 = _run(p, st, [1] * 5)
+        f5, n5 = _run(p, st, [5])
+        np.testing.assert_array_equal(f5, f1, err_msg=str(shape))
+        np.testing.assert_array_equal(n5, n1, err_msg=str(shape))
+        f4, _ = _run(p, st, [2, 3])
+        np.testing.assert_array_equal(f4, f1, err_msg=str(shape))
+
+
+@pytest.mark.parametrize("storage", [scmc.F64, scmc.F32, scmc.F16_NODE])
+def test_block_graph_equals_single_steps(storage):
+    shape = (21, 30, 45)
+    p, st = _problem(shape, 6, storage), _state(shape)
+    f1, _ = _run(p, st, [1] * 13)
+    fg, _ = _run(p, st, [7, 6], graph=3)  # two replays and a single step, then two more
+    np.testing.assert_array_equal(fg, f1)
+
+
+def test_block_large_lattice_equals_single_steps():
+    """Many columns and chunks, moments beyond the slab threshold of FP16."""
+    shape = (190, 176, 180)
+    for storage in (scmc.F32, scmc.F16_OFF):
+        p, st = _problem(shape, 6, storage), _state(shape)
+        f1, _ = _run(p, st, [1] * 3)
+        f3, _ = _run(p, st, [3])
+        assert np.array_equal(f3, f1)
