@@ -99,8 +99,8 @@ __device__ __forceinline__ void lds_force(
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const R tA = (R)(PSI == 0 ? cB[c] : sA[c]), tB = (R)(PSI == 0 ? cA[c] : sB[c]);
-        FA[c] = -gAB * nA * (R)cA[c] - gAA * pA * tA;
-        FB[c] = -gBA * nB * (R)cB[c] - gBB * pB * tB;
+        FA[c] = sc_force(gAB, nA, (R)cA[c], gAA, pA, tA);
+        FB[c] = sc_force(gBA, nB, (R)cB[c], gBB, pB, tB);
     }
 }
 

@@ -45,6 +45,21 @@ struct SiteRng {
     }
 };
 
+// Value of the other component's lane, where two neighbouring lanes share a
+// node, one per component.
+__device__ __forceinline__ int swap_bits(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
+}
+__device__ __forceinline__ float swap_pair(float v) {
+    return __builtin_bit_cast(float, swap_bits(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double swap_pair(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)swap_bits((int)(unsigned)b);
+    const int hi = swap_bits((int)(b >> 32));
+    return __builtin_bit_cast(double, ((long long)hi << 32) | lo);
+}
+
 template <class R, int PSI> __device__ __forceinline__ R psi_of(R n) {
     if constexpr (PSI == 0) {
         return n;
@@ -102,6 +117,14 @@ __device__ __forceinline__ void site_density(const R (&f)[2][Lattice<D>::Q],
     }
     nA = (R)a;
     nB = (R)b;
+}
+
+// One component of the force: -g n_J c_K - g_JJ psi_J s_J (c, s: stencil sums)
+template <class R> __device__ __forceinline__ R sc_force(R g, R n, R c, R gs, R psi, R s) {
+#pragma clang fp contract(off)
+    const R self = gs * psi * s, gn = -g * n;
+    if constexpr (std::is_same<R, float>::value) return __builtin_fmaf(gn, c, -self);
+    else return __builtin_fma(gn, c, -self);
 }
 
 // Stencil sums of eq. sc_force around site (x, y, z), with the stencil
@@ -168,8 +191,8 @@ __device__ __forceinline__ void site_force_fn(const Member &m, int x, int y, int
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const R tA = (R)(PSI == 0 ? cB[k] : sA[k]), tB = (R)(PSI == 0 ? cA[k] : sB[k]);
-        FA[k] = -gAB * nA * (R)cA[k] - gAA * pA * tA;
-        FB[k] = -gBA * nB * (R)cB[k] - gBB * pB * tB;
+        FA[k] = sc_force(gAB, nA, (R)cA[k], gAA, pA, tA);
+        FB[k] = sc_force(gBA, nB, (R)cB[k], gBB, pB, tB);
     }
 }
 
@@ -277,37 +300,50 @@ __device__ __forceinline__ void site_collide(const Member &m,
 constexpr int NMOM = 7;  // n_A, n_B, j_x, j_y, j_z, rem(n_A), rem(n_B)
 
 // Raw moments of one component's populations, FP64: n = sum_i f_i and
-// j = sum_i xi_i f_i, summed in groups of equal xi_z (+1, 0, -1), each in the
-// order of i: a march through the z-planes that receives the populations of
-// plane z - 1 first, then those of plane z and of plane z + 1 forms the same
-// sums, also where they round (FP64 storage).
-template <class R>
-__device__ __forceinline__ void add_group(int cz, const R (&f)[19], double &g, double &jx,
-                                          double &jy) {
-    using L = Lattice<3>;
-#pragma unroll
-    for (int i = 0; i < 19; ++i) {
-        if (L::CZ[i] != cz) continue;
-        g += (double)f[i];
-        if (L::CX[i]) jx += (double)L::CX[i] * (double)f[i];
-        if (L::CY[i]) jy += (double)L::CY[i] * (double)f[i];
+// j = sum_i xi_i f_i.  In 3D the populations that arrive from one neighbouring
+// column are added first, those from plane z - 1, z and z + 1 in this order
+// (S; their difference D enters j_z), then the columns: the sums of a march
+// through the z-planes that receives one S and D per column (moment_impl.h).
+struct ColumnSums {
+    double S[4], D[4];      // from x - 1, x + 1, y - 1, y + 1
+    double own, ownD;       // the node's own column
+    double nd, xd, yd;      // the four diagonal columns: their n, j_x, j_y
+    __device__ __forceinline__ void diag(double q7, double q8, double q9, double q10) {
+        const double s = q7 - q8, t = q9 - q10;
+        nd = (q7 + q8) + (q9 + q10);
+        xd = s + t;
+        yd = s - t;
     }
-}
+    __device__ __forceinline__ void total(double &n, double &jx, double &jy, double &jz) const {
+        n = (own + ((S[0] + S[1]) + (S[2] + S[3]))) + nd;
+        jx = (S[0] - S[1]) + xd;
+        jy = (S[2] - S[3]) + yd;
+        jz = ownD + ((D[0] + D[1]) + (D[2] + D[3]));
+    }
+};
+// directions of column sum a: from below (xi_z = 1), in the plane, from above
+__device__ constexpr int COL_UP[4] = {11, 14, 15, 18};
+__device__ constexpr int COL_MID[4] = {1, 2, 3, 4};
+__device__ constexpr int COL_DOWN[4] = {13, 12, 17, 16};
 
 template <int D, class R>
 __device__ __forceinline__ void raw_moments(const R (&f)[Lattice<D>::Q], double &n, double &jx,
                                             double &jy, double &jz) {
     using L = Lattice<D>;
-    jx = jy = jz = 0;
     if constexpr (D == 3) {
-        double gp = 0, g0 = 0, gm = 0;
-        add_group(1, f, gp, jx, jy);
-        add_group(0, f, g0, jx, jy);
-        add_group(-1, f, gm, jx, jy);
-        n = (gp + g0) + gm;
-        jz = gp - gm;
+        ColumnSums c;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const double up = f[COL_UP[a]], down = f[COL_DOWN[a]];
+            c.S[a] = (up + (double)f[COL_MID[a]]) + down;
+            c.D[a] = up - down;
+        }
+        c.own = ((double)f[5] + (double)f[0]) + (double)f[6];
+        c.ownD = (double)f[5] - (double)f[6];
+        c.diag(f[7], f[8], f[9], f[10]);
+        c.total(n, jx, jy, jz);
     } else {
-        n = 0;
+        n = jx = jy = jz = 0;
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
             n += (double)f[i];
@@ -380,28 +416,45 @@ __device__ __forceinline__ void unpack_rem(unsigned w, R (&mm)[NMOM]) {
 // values with the exact n_J: rounded weights (their binary sum is not exactly
 // 1) and re-rounded sums would otherwise bias the mass by the same relative
 // amount every step.
+// The roundings are spelt out (fused multiply-adds where they are meant, no
+// contraction elsewhere), so that every kernel that collides a node, and each
+// of its components, forms the same bits.  p is the momentum (n_A + n_B) u,
+// inv = 1 / (n_A + n_B).
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) {
+    return __builtin_fma(a, b, c);
+}
+
 template <int D, class R, class Emit>
-__device__ __forceinline__ void collide_tau1_component(R nJ, R remJ, const R (&F)[3], R ux, R uy,
-                                                       R uz, Emit &&emit) {
+__device__ __forceinline__ void collide_tau1_component(R nJ, R remJ, const R (&F)[3],
+                                                       const R (&p)[3], R inv, Emit &&emit) {
+#pragma clang fp contract(off)
     using L = Lattice<D>;
     constexpr Opposite<D> OP = Opposite<D>::make();
-    const R uu = ux * ux + uy * uy + uz * uz;
-    const R uF = ux * F[0] + uy * F[1] + uz * F[2];
-    const R a = nJ * (R(1) - R(1.5) * uu) - R(1.5) * uF;
+    const R u[3] = {p[0] * inv, p[1] * inv, D == 3 ? p[2] * inv : R(0)};
+    R uu = fma_r(u[0], u[0], u[1] * u[1]), uF = fma_r(u[0], F[0], u[1] * F[1]);
+    if (D == 3) {
+        uu = fma_r(u[2], u[2], uu);
+        uF = fma_r(u[2], F[2], uF);
+    }
+    const R a = fma_r(nJ, fma_r(R(-1.5), uu, R(1)), R(-1.5) * uF);
     double moving = 0;
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
         const int ib = OP.opp[i];
         if (ib < i) continue;
-        R xu = 0, xF = 0;
-        if (L::CX[i]) { xu += (R)L::CX[i] * ux; xF += (R)L::CX[i] * F[0]; }
-        if (L::CY[i]) { xu += (R)L::CY[i] * uy; xF += (R)L::CY[i] * F[1]; }
-        if (D == 3 && L::CZ[i]) { xu += (R)L::CZ[i] * uz; xF += (R)L::CZ[i] * F[2]; }
+        const int c[3] = {L::CX[i], L::CY[i], L::CZ[i]};
+        const int k0 = c[0] ? 0 : c[1] ? 1 : 2;  // the one or two axes of xi
+        const int k1 = k0 == 0 && c[1] ? 1 : k0 < 2 && c[2] ? 2 : k0;
+        R xu = c[k0] > 0 ? u[k0] : -u[k0], xF = c[k0] > 0 ? F[k0] : -F[k0];
+        if (k1 != k0) {
+            xu = fma_r(c[k1] > 0 ? inv : -inv, p[k1], xu);
+            xF = c[k1] > 0 ? xF + F[k1] : xF - F[k1];
+        }
         const R w = (R)L::W[i];
-        const R t = nJ * xu;
-        const R E = w * (a + R(4.5) * xu * (t + xF));
-        const R O = w * (R(3) * t + R(1.5) * xF);
-        const R fp = emit(i, E + O), fm = emit(ib, E - O);
+        const R X = fma_r(R(4.5) * xu, fma_r(nJ, xu, xF), a);
+        const R O = w * fma_r(R(1.5), xF, R(3) * (nJ * xu));
+        const R fp = emit(i, fma_r(w, X, O)), fm = emit(ib, fma_r(w, X, -O));
         moving += (double)fp + (double)fm;
     }
     const double nJx = (double)nJ + (double)remJ;
@@ -412,12 +465,12 @@ template <int D, class R, class Emit>
 __device__ __forceinline__ void collide_tau1_emit(const R (&mom)[NMOM], const R (&FA)[3],
                                                   const R (&FB)[3], Emit &&emit) {
     const R inv = R(1) / (mom[0] + mom[1]);
-    const R ux = (mom[2] + R(0.5) * (FA[0] + FB[0])) * inv;
-    const R uy = (mom[3] + R(0.5) * (FA[1] + FB[1])) * inv;
-    const R uz = D == 3 ? (mom[4] + R(0.5) * (FA[2] + FB[2])) * inv : R(0);
+    R p[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p[k] = fma_r(R(0.5), FA[k] + FB[k], mom[2 + k]);
 #pragma unroll
     for (int J = 0; J < 2; ++J)
-        collide_tau1_component<D, R>(mom[J], mom[5 + J], J == 0 ? FA : FB, ux, uy, uz,
+        collide_tau1_component<D, R>(mom[J], mom[5 + J], J == 0 ? FA : FB, p, inv,
                                      [&](int i, R v) { return emit(J, i, v); });
 }
 
