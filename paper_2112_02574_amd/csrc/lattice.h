@@ -142,6 +142,8 @@ struct StoreF64 {
     static constexpr int BYTES = 8;
     __device__ __forceinline__ static R from_raw(T v, R) { return v; }
     __device__ __forceinline__ static T to_raw(R v, R) { return v; }
+    __device__ __forceinline__ static T encode(R v, R, R) { return v; }
+    __device__ __forceinline__ static R decode(T v, R, R) { return v; }
     __device__ __forceinline__ static R stored(R v, R, R) { return v; }
     __device__ __forceinline__ static R load(const T *p, long i, R) { return p[i]; }
     __device__ __forceinline__ static void store(T *p, long i, R v, R) {
@@ -156,6 +158,8 @@ struct StoreF32 {
     static constexpr int BYTES = 4;
     __device__ __forceinline__ static R from_raw(T v, R) { return v; }
     __device__ __forceinline__ static T to_raw(R v, R) { return v; }
+    __device__ __forceinline__ static T encode(R v, R, R) { return v; }
+    __device__ __forceinline__ static R decode(T v, R, R) { return v; }
     __device__ __forceinline__ static R stored(R v, R, R) { return v; }
     __device__ __forceinline__ static R load(const T *p, long i, R) { return p[i]; }
     __device__ __forceinline__ static void store(T *p, long i, R v, R) {
@@ -181,12 +185,17 @@ struct StoreF16 {
         const T h = __half_as_ushort(__float2half_rn(v - ref));
         __builtin_nontemporal_store(h, p + i);
     }
-    // The value that a load finds of a stored one, with the reference w n0
-    // inside both roundings, as the compiler contracts to_raw and from_raw
-    // around the product in the two passes.
-    __device__ __forceinline__ static R stored(R v, R w, R n0) {
-        const T h = __half_as_ushort(__float2half_rn(__builtin_fmaf(-w, n0, v)));
+    // encode / decode: to_raw / from_raw with the reference w n0 inside both
+    // roundings, as the compiler contracts them around the product in the two
+    // passes; stored: the value that a load finds of a stored one
+    __device__ __forceinline__ static T encode(R v, R w, R n0) {
+        return __half_as_ushort(__float2half_rn(__builtin_fmaf(-w, n0, v)));
+    }
+    __device__ __forceinline__ static R decode(T h, R w, R n0) {
         return __builtin_fmaf(w, n0, __half2float(__ushort_as_half(h)));
+    }
+    __device__ __forceinline__ static R stored(R v, R w, R n0) {
+        return decode(encode(v, w, n0), w, n0);
     }
     // Node storage (offsets from the node's own rest equilibrium, which are
     // small where the flow is slow): the offset is scaled by 2^10 before it
@@ -252,8 +261,14 @@ struct StoreBF16 {
         const T h = f32_to_bf16_dev(v - ref);
         __builtin_nontemporal_store(h, p + i);
     }
-    __device__ __forceinline__ static R stored(R v, R w, R n0) {  // as StoreF16::stored
-        return __builtin_fmaf(w, n0, bf16_to_f32(f32_to_bf16_dev(__builtin_fmaf(-w, n0, v))));
+    __device__ __forceinline__ static T encode(R v, R w, R n0) {  // as in StoreF16
+        return f32_to_bf16_dev(__builtin_fmaf(-w, n0, v));
+    }
+    __device__ __forceinline__ static R decode(T h, R w, R n0) {
+        return __builtin_fmaf(w, n0, bf16_to_f32(h));
+    }
+    __device__ __forceinline__ static R stored(R v, R w, R n0) {
+        return decode(encode(v, w, n0), w, n0);
     }
     // node storage: bfloat16 has the binary32 exponent range, no scale
     __device__ __forceinline__ static T to_node(R v, R ref) { return to_raw(v, ref); }

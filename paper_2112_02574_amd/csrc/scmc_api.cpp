@@ -1610,6 +1610,17 @@ static scmc_problem flat_problem(const scmc_problem &p, int lx) {
     return q;
 }
 
+// k steps of the flat interface, which stays uniform along y and z.
+static int flat_steps(scmc_sim *s, int64_t k) {
+    Common &c = s->c;
+    if (!row_steps_supported(c.key, s->lat.m)) return scmc_step(s, k);
+    const int to = c.cur ^ (int)(k & 1);
+    HIPCHK(c, launch_row_steps(c.key, s->lat.m, c.pop[c.cur], c.pop[to], (int)k, c.stream));
+    c.cur = to;
+    c.step += k;
+    return SCMC_OK;
+}
+
 int scmc_flat_workspace_bytes(const scmc_problem *p, int lx, size_t *out) {
     if (!p || !out) return SCMC_EINVAL;
     const scmc_problem q = flat_problem(*p, lx);
@@ -1646,7 +1657,7 @@ int scmc_flat_equilibrium(const scmc_problem *p, int lx, const double *guess,
     bool converged = false;
     while (!rc && !converged && done < max_steps) {
         const int64_t k = std::min<int64_t>(2048, max_steps - done);
-        rc = scmc_step(s, k);
+        rc = flat_steps(s, k);
         if (!rc) rc = scmc_get_fields(s, nA.data(), nB.data(), nullptr);
         if (rc) break;
         done += k;

@@ -152,6 +152,12 @@ struct MomShape {
 // fields), int in_slot, int out_slot (slots of their (n_A, n_B) pairs).
 bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape);
 
+// ---- steps of a lattice uniform along y and z (row_kernels.hip)
+bool row_steps_supported(const StepKey &k, const Member &m);
+// nsteps >= 1 steps from src; dst (may be src) gets the whole lattice's state
+hipError_t launch_row_steps(const StepKey &k, const Member &m, const void *src, void *dst,
+                            int nsteps, hipStream_t st);
+
 // ---- bandwidth ceiling (ceiling_kernels.hip): the 2Q population planes of
 // src copied to dst with the pull shifts, one site per lane; elements of
 // `bytes` bytes (8, 4 or 2)
