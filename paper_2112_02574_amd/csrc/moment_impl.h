@@ -109,13 +109,13 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
     }
     const int pbytes = m.N * SZ;
     const __amdgpu_buffer_rsrc_t ipr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(in + (long)in_slot * m.N), (short)0, 2 * pbytes, BUF_DATA_FORMAT_32);
+        (void *)(in + m.dens_off + (long)in_slot * m.N), (short)0, 2 * pbytes, BUF_DATA_FORMAT_32);
     const __amdgpu_buffer_rsrc_t imr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(in + 2L * m.N), (short)0, (F64 ? 3 : 4) * pbytes, BUF_DATA_FORMAT_32);
+        (void *)(in + m.dens_off + 2L * m.N), (short)0, (F64 ? 3 : 4) * pbytes, BUF_DATA_FORMAT_32);
     const __amdgpu_buffer_rsrc_t opr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(out + (long)out_slot * m.N), (short)0, 2 * pbytes, BUF_DATA_FORMAT_32);
+        (void *)(out + m.dens_off + (long)out_slot * m.N), (short)0, 2 * pbytes, BUF_DATA_FORMAT_32);
     const __amdgpu_buffer_rsrc_t omr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(out + 2L * m.N), (short)0, (F64 ? 3 : 4) * pbytes, BUF_DATA_FORMAT_32);
+        (void *)(out + m.dens_off + 2L * m.N), (short)0, (F64 ? 3 : 4) * pbytes, BUF_DATA_FORMAT_32);
 
     const R gx = (R)(J ? m.g[1][0] : m.g[0][1]), gs = (R)(J ? m.g[1][1] : m.g[0][0]);
     const bool self = (m.self_on >> J) & 1, any_self = m.self_on & 3;
@@ -332,20 +332,40 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
     round(std::integral_constant<int, 2>{}, len + 1);
 }
 
+// Block b of a member's launch: its column and chunk.
 template <int ORDER, class ST, int PSI, bool NODE>
-__global__ void __launch_bounds__(MOM_THREADS)
-    k_mom_step(Member m, MomShape g, const typename ST::R *__restrict__ in,
-               typename ST::R *__restrict__ out, int in_slot, int out_slot) {
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
-    const int tx = t % g.ntx, q = t / g.ntx, ty = q % g.nty, c = q / g.nty;
+__device__ __forceinline__ void mom_block(const Member &m, const MomShape &g, int b,
+                                          const typename ST::R *__restrict__ in,
+                                          typename ST::R *__restrict__ out, int in_slot,
+                                          int out_slot) {
+    const int tx = b % g.ntx, q = b / g.ntx, ty = q % g.nty, c = q / g.nty;
     const int x0 = tx * g.w, y0 = ty * g.h, z0 = c * g.zc;
     mom_column<ORDER, ST, PSI, NODE>(m, in, out, in_slot, out_slot, x0, y0, z0,
                                      min(g.w, m.nx - x0), min(g.h, m.ny - y0),
                                      min(g.zc, m.nz - z0));
 }
 
+template <int ORDER, class ST, int PSI, bool NODE>
+__global__ void __launch_bounds__(MOM_THREADS)
+    k_mom_step(Member m, MomShape g, const typename ST::R *__restrict__ in,
+               typename ST::R *__restrict__ out, int in_slot, int out_slot) {
+    mom_block<ORDER, ST, PSI, NODE>(m, g, xcd_remap(blockIdx.x, gridDim.x), in, out, in_slot,
+                                    out_slot);
+}
+
+template <int ORDER, class ST, int PSI>
+__global__ void __launch_bounds__(MOM_THREADS)
+    kb_mom_step(const Member *__restrict__ members, MomList list,
+                const typename ST::R *__restrict__ in, typename ST::R *__restrict__ out) {
+    const int b = xcd_remap(blockIdx.x, gridDim.x), lane = threadIdx.x & 63;
+    const bool mine = lane < list.n && list.e[lane].first <= b;
+    const int i = __builtin_amdgcn_readfirstlane(__popcll(__ballot(mine)) - 1);
+    const Member m = members[list.e[i].member];
+    mom_block<ORDER, ST, PSI, false>(m, list.e[i].g, b - list.e[i].first, in, out, 0, 0);
+}
+
 struct MomKernel {
-    void *func = nullptr;
+    void *func = nullptr, *batch = nullptr;
     int rows = 0;  // of its ring (MomGeom::ROWS)
 };
 
@@ -355,14 +375,19 @@ template <class ST, int ORDER> struct MomOps {
 
 template <class ST, int ORDER> MomKernel MomOps<ST, ORDER>::kernel(const StepKey &k) {
     using R = typename ST::R;
-    auto pick = [&](auto Nc) {
-        constexpr bool N = decltype(Nc)::value;
-        return k.psi ? MomKernel{(void *)&k_mom_step<ORDER, ST, 1, N>, MomGeom<ORDER, R, 1>::ROWS}
-                     : MomKernel{(void *)&k_mom_step<ORDER, ST, 0, N>, MomGeom<ORDER, R, 0>::ROWS};
+    auto pick = [&](auto Pc) {
+        constexpr int P = decltype(Pc)::value;
+        MomKernel q;
+        q.rows = MomGeom<ORDER, R, P>::ROWS;
+        if (!k.node) {
+            q.func = (void *)&k_mom_step<ORDER, ST, P, false>;
+            q.batch = (void *)&kb_mom_step<ORDER, ST, P>;
+        } else if constexpr (sizeof(typename ST::T) == 2) {
+            q.func = (void *)&k_mom_step<ORDER, ST, P, true>;
+        }
+        return q;
     };
-    if (!k.node) return pick(std::false_type{});
-    if constexpr (sizeof(typename ST::T) == 2) return pick(std::true_type{});
-    return MomKernel{};
+    return k.psi ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 0>{});
 }
 
 }  // namespace scmc

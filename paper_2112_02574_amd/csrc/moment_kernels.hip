@@ -27,6 +27,34 @@ SCMC_MOM_COMBOS(SCMC_EXTERN)
 // 24x10x2 11.6, 24x16x4 18.5.  Both fields of a step lie in the caches up to
 // about 170^3, and beyond that its 48 B per site still stream faster than it
 // computes.
+// The search below runs over columns for a given number of planes per chunk
+// (mom_columns) and over that number; the members of a batched launch share
+// the chunk length, and their workgroups the rounds.
+static constexpr double kPlaneUs = 27, kFillPlanes = 3.5;  // in units of a wavefront's 0.06 us
+
+// The fewest wavefront-planes per plane of the member: columns, largest first.
+static MomShape mom_columns(const Member &m, int order, int rows) {
+    const int r = order == 4 ? 1 : 2;
+    MomShape best{};
+    double best_cost = 1e300;
+    for (int ntx = 1; ntx <= m.nx; ++ntx) {
+        const int w = (m.nx + ntx - 1) / ntx;
+        if (w < 8 && ntx > 1) break;
+        if ((m.nx + w - 1) / w != ntx || w + 2 + 2 * r > MOM_PW) continue;
+        int h = std::min({m.ny, MOM_EXT / (w + 2) - 2, rows - 2 - 2 * r});
+        if (h < 1) continue;
+        const int nty = (m.ny + h - 1) / h;
+        h = (m.ny + nty - 1) / nty;
+        const int waves = (2 * (w + 2) * (h + 2) + 63) / 64;
+        const double cost = (double)ntx * nty * (kPlaneUs + waves);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = MomShape{w, h, m.nz, ntx, nty, 1};
+        }
+    }
+    return best;
+}
+
 static MomShape mom_shape(const Member &m, int order, int rows, int ncu) {
     const int r = order == 4 ? 1 : 2;
     MomShape best{};
@@ -46,7 +74,7 @@ static MomShape mom_shape(const Member &m, int order, int rows, int ncu) {
             if ((m.nz + zc - 1) / zc != nc) continue;
             const long blocks = (long)ntx * nty * nc;
             const double cost =
-                (double)((blocks + ncu - 1) / ncu) * (zc + 3.5) * (27 + waves);
+                (double)((blocks + ncu - 1) / ncu) * (zc + kFillPlanes) * (kPlaneUs + waves);
             if (cost < best_cost) {
                 best_cost = cost;
                 best = MomShape{w, h, zc, ntx, nty, nc};
@@ -56,9 +84,9 @@ static MomShape mom_shape(const Member &m, int order, int rows, int ncu) {
     return best;
 }
 
-bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape) {
-    if (k.dim != 3 || (k.order != 4 && k.order != 6) || k.sr) return false;
+static MomKernel mom_kernel(const StepKey &k) {
     MomKernel f;
+    if (k.dim != 3 || (k.order != 4 && k.order != 6) || k.sr) return f;
     auto go = [&](auto stv) {
         using ST = decltype(stv);
         f = k.order == 4 ? MomOps<ST, 4>::kernel(k) : MomOps<ST, 6>::kernel(k);
@@ -69,20 +97,75 @@ bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape
         case ST_F16: go(StoreF16{}); break;
         case ST_BF16: go(StoreBF16{}); break;
     }
-    if (!f.func) return false;
+    return f;
+}
+
+static int compute_units() {
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         ncu < 1)
         ncu = 256;
-    *shape = mom_shape(m, k.order, f.rows, ncu);
+    return ncu;
+}
+
+// Threads of a workgroup: two lanes per node of the rimmed column; two passes
+// load its ring plane.
+static int mom_threads(const StepKey &k, const MomShape &g) {
+    const int r2 = k.order == 4 ? 4 : 6;
+    return (std::max(2 * (g.w + 2) * (g.h + 2), (g.w + r2) * (g.h + r2)) + 63) / 64 * 64;
+}
+
+bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape) {
+    const MomKernel f = mom_kernel(k);
+    if (!f.func) return false;
+    *shape = mom_shape(m, k.order, f.rows, compute_units());
     if (shape->w < 1) return false;
-    // two lanes per node of the rimmed column; two passes load its ring plane
-    const int rim = (shape->w + 2) * (shape->h + 2), r2 = k.order == 4 ? 4 : 6;
-    const int ring = (shape->w + r2) * (shape->h + r2);
     node->func = f.func;
     node->grid = dim3(shape->ntx * shape->nty * shape->nchunks);
-    node->block = dim3((std::max(2 * rim, ring) + 63) / 64 * 64, 1, 1);
+    node->block = dim3(mom_threads(k, *shape), 1, 1);
+    node->shmem = 0;
+    return true;
+}
+
+bool node_batch_mom_step(const StepKey &k, const std::vector<Member> &ms, int first_member,
+                         NodeLaunch *node, MomList *list) {
+    const MomKernel f = mom_kernel(k);
+    if (!f.batch || ms.empty() || ms.size() > (size_t)MOM_LIST) return false;
+    const int ncu = compute_units();
+    std::vector<MomShape> g;
+    int nzmax = 1;
+    for (const Member &m : ms) {
+        g.push_back(mom_columns(m, k.order, f.rows));
+        if (g.back().w < 1) return false;
+        nzmax = std::max(nzmax, m.nz);
+    }
+    double best_cost = 1e300;
+    int best = 1;
+    for (int len = 1; len <= nzmax; ++len) {
+        long blocks = 0;
+        for (size_t i = 0; i < ms.size(); ++i)
+            blocks += (long)g[i].ntx * g[i].nty * ((ms[i].nz + len - 1) / len);
+        const double cost = (double)((blocks + ncu - 1) / ncu) * (len + kFillPlanes);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = len;
+        }
+    }
+    list->n = (int)ms.size();
+    int first = 0, threads = 64;
+    for (size_t i = 0; i < ms.size(); ++i) {
+        MomShape q = g[i];
+        q.nchunks = (ms[i].nz + best - 1) / best;
+        q.zc = (ms[i].nz + q.nchunks - 1) / q.nchunks;
+        q.nchunks = (ms[i].nz + q.zc - 1) / q.zc;
+        list->e[i] = MomList::Entry{first, first_member + (int)i, q};
+        first += q.ntx * q.nty * q.nchunks;
+        threads = std::max(threads, mom_threads(k, q));
+    }
+    node->func = f.batch;
+    node->grid = dim3(first);
+    node->block = dim3(threads, 1, 1);
     node->shmem = 0;
     return true;
 }

@@ -218,12 +218,23 @@ struct scmc_sim {
 // One launch of the batched two-pass: pass 1 or 2 over tiles [t0, t0 + n),
 // one workgroup per tile; nt_all: pass 1 with every load non-temporal.
 // member >= 0: the chunk is that member alone, launched like a single
-// lattice (launch_member_pass, with m its description) instead.
+// lattice (node_member_pass, with m its description) instead.
 struct BatchOp {
     int pass, t0, n;
     bool nt_all = false;
     int member = -1;
     Member m{};
+};
+
+// Ops [op0, op1) of consecutive members (from `member` on), which advance a
+// block of steps before the next group starts.  mom: the steps between the
+// first pass 1 and the last pass 2 stay in the moment field.
+struct BatchGroup {
+    size_t op0 = 0, op1 = 0;
+    int member = 0;
+    bool mom = false;
+    NodeLaunch node{};
+    MomList list{};
 };
 
 struct scmc_batch {
@@ -238,6 +249,7 @@ struct scmc_batch {
     // The launches of one two-pass step (batch_set_ops); empty for the fused
     // designs, which run the whole list in one persistent launch.
     std::vector<BatchOp> ops;
+    std::vector<BatchGroup> groups;  // runs of ops that step together
 };
 
 namespace {
@@ -925,81 +937,109 @@ int direct_steps_sim(scmc_sim *s, int64_t k) {
     return rc;
 }
 
-hipError_t launch_op(scmc_batch *b, const BatchOp &o, const void *src, void *dst) {
-    const Common &c = b->c;
-    return o.member >= 0 ? launch_member_pass(c.key, o.m, src, dst, c.dens, o.pass, o.nt_all,
-                                              c.stream)
-                         : launch_batch_two_pass(c.key, b->d_members, b->d_tiles + o.t0, o.n,
-                                                 src, dst, c.dens, o.n, c.stream, o.pass,
-                                                 o.nt_all);
-}
-
-int direct_step_batch(scmc_batch *b) {
+// One op of the batched two-pass from src to dst with the moment field (its
+// base, to which members add dens_off) at field.
+template <class Emit>
+int emit_op(scmc_batch *b, const BatchOp &o, const void *src, void *dst, void *field,
+            Emit &&emit) {
     Common &c = b->c;
-    const void *src = c.pop[c.cur];
-    void *dst = c.pop[1 - c.cur];
-    hipError_t e = hipSuccess;
-    if (c.kernel == SCMC_KERNEL_FUSED) {
-        e = launch_batch_fused(c.key, b->d_members, b->d_tiles, b->ntiles, src, dst, c.tile,
-                               b->grid, c.stream);
+    std::vector<void *> args;
+    NodeLaunch nl{};
+    Member m = o.m;
+    const Member *dm = b->d_members;
+    const Tile *dt = b->d_tiles + o.t0;
+    int nt = o.n;
+    if (o.member >= 0) {  // a chunk of one member, as a single lattice
+        if (!node_member_pass(c.key, o.m, o.pass, o.nt_all, &nl))
+            return fail(c, SCMC_EUNSUPPORTED, "no kernel for a member pass");
+        args = {(void *)&m, (void *)&src};
+    } else {
+        NodeLaunch dn{}, sn{}, dna{};
+        if (!node_batch_two_pass(c.key, o.n, &dn, &sn, &dna))  // one workgroup per tile
+            return fail(c, SCMC_EUNSUPPORTED, "no kernel for this batch");
+        nl = o.pass == 1 ? (o.nt_all ? dna : dn) : sn;
+        args = {(void *)&dm, (void *)&dt, (void *)&nt, (void *)&src};
     }
-    for (size_t k = 0; e == hipSuccess && k < b->ops.size(); ++k)
-        e = launch_op(b, b->ops[k], src, dst);
-    if (e != hipSuccess)
-        return fail(c, SCMC_EDEVICE, "batch step launch: %s",
-                    hipGetErrorString(e));
-    c.cur ^= 1;
-    return SCMC_OK;
+    if (o.pass == 2) args.push_back((void *)&dst);
+    args.push_back((void *)&field);
+    return emit(nl, args);
 }
 
-// k steps of the batched two-pass, chunk by chunk: each chunk (the pass 1 and
-// pass 2 ops that batch_set_ops pairs) advances k steps before the next one
-// starts.  Members are independent lattices, so the order changes no bit of
-// any member's result, and every member is k steps further on return; a
-// chunk's next pass 1 then reads the populations its pass 2 has just
-// written, part of them still in the Infinity Cache, as a lattice stepped on
-// its own does.  The fused design (no ops) runs step by step.
+// k steps of the batched two-pass from buffer par, group by group: each group
+// (whole chunks, whose pass 1 and pass 2 ops batch_set_ops pairs) advances k
+// steps before the next one starts.  Members are independent lattices, so the
+// order changes no bit of any member's result, and every member is k steps
+// further on return; a group's next step then reads what its last one has just
+// written, part of it still in the Infinity Cache, as a lattice stepped on its
+// own does.  With mom set the steps between stay in the moment field, as in
+// mom_steps; the second field is the group's own part of the population
+// buffer that its pass 1 does not read.
+template <class Emit> int batch_steps(scmc_batch *b, int64_t k, int par, Emit &&emit) {
+    Common &c = b->c;
+    int rc = SCMC_OK;
+    for (BatchGroup &g : b->groups) {
+        if (k >= 2 && g.mom) {
+            const int last = par ^ (int)((k - 1) & 1);
+            const Member &m0 = b->lats[g.member].m;
+            const scmc_problem &p0 = b->lats[g.member].p;
+            char *own = (char *)c.pop[1 - par] + m0.pop_off * (int64_t)storage_bytes(p0.storage);
+            void *field[2] = {c.dens, own - m0.dens_off * (int64_t)real_bytes(p0.storage)};
+            int at = (int)((k - 1) & 1);
+            for (size_t j = g.op0; j < g.op1 && !rc; j += 2)
+                rc = emit_op(b, b->ops[j], c.pop[par], c.pop[1 - par], field[at], emit);
+            const Member *dm = b->d_members;
+            for (int64_t t = 1; t < k && !rc; ++t, at ^= 1) {
+                std::vector<void *> a = {(void *)&dm, (void *)&g.list, (void *)&field[at],
+                                         (void *)&field[1 - at]};
+                rc = emit(g.node, a);
+            }
+            for (size_t j = g.op0 + 1; j < g.op1 && !rc; j += 2)
+                rc = emit_op(b, b->ops[j], c.pop[last], c.pop[1 - last], field[0], emit);
+            continue;
+        }
+        for (size_t j = g.op0; j < g.op1 && !rc; j += 2)  // chunk by chunk
+            for (int64_t t = 0; t < k && !rc; ++t) {
+                const int cu = par ^ (int)(t & 1);
+                rc = emit_op(b, b->ops[j], c.pop[cu], c.pop[1 - cu], c.dens, emit);
+                if (!rc) rc = emit_op(b, b->ops[j + 1], c.pop[cu], c.pop[1 - cu], c.dens, emit);
+            }
+    }
+    return rc;
+}
+
+// k steps of a batch outside graphs; the fused design (no ops) runs step by step.
 int direct_steps_batch(scmc_batch *b, int64_t k) {
     Common &c = b->c;
     if (b->ops.empty()) {
         for (int64_t t = 0; t < k; ++t) {
-            const int rc = direct_step_batch(b);
-            if (rc) return rc;
+            const hipError_t e = launch_batch_fused(c.key, b->d_members, b->d_tiles, b->ntiles,
+                                                    c.pop[c.cur], c.pop[1 - c.cur], c.tile,
+                                                    b->grid, c.stream);
+            if (e != hipSuccess)
+                return fail(c, SCMC_EDEVICE, "batch step launch: %s", hipGetErrorString(e));
+            c.cur ^= 1;
         }
         return SCMC_OK;
     }
-    hipError_t e = hipSuccess;
-    for (size_t j = 0; e == hipSuccess && j + 1 < b->ops.size(); j += 2)
-        for (int64_t t = 0; e == hipSuccess && t < k; ++t) {
-            const int cu = c.cur ^ (int)(t & 1);
-            e = launch_op(b, b->ops[j], c.pop[cu], c.pop[1 - cu]);
-            if (e == hipSuccess) e = launch_op(b, b->ops[j + 1], c.pop[cu], c.pop[1 - cu]);
-        }
-    if (e != hipSuccess)
-        return fail(c, SCMC_EDEVICE, "batch step launch: %s", hipGetErrorString(e));
-    if (k & 1) c.cur ^= 1;
-    return SCMC_OK;
+    const int rc = batch_steps(b, k, c.cur, [&](const NodeLaunch &nl, std::vector<void *> &args) {
+        const hipError_t e =
+            hipLaunchKernel(nl.func, nl.grid, nl.block, args.data(), nl.shmem, c.stream);
+        return e == hipSuccess
+                   ? SCMC_OK
+                   : fail(c, SCMC_EDEVICE, "batch step launch: %s", hipGetErrorString(e));
+    });
+    if (!rc && (k & 1)) c.cur ^= 1;
+    return rc;
 }
 
 // Build an executable graph of k steps starting from buffer `par`.
-// args(step, node, par) fills the kernel argument pointer arrays.
-struct ArgPack {
-    Member m;
-    const Member *members;
-    const Tile *tiles;
-    int ntiles;
-    const void *src;
-    void *dst;
-    void *dens;
-    int tile[3];
-};
-
-// A single lattice passes chunks {0, 0}; a batch either its two-pass
-// launches (ops) or, for the fused designs, chunks {0, ntiles}.
+// A single lattice passes chunks {0, 0} and, to run on the moment field where
+// it can, itself (sim); a batch either itself for its two-pass launches
+// (two_pass) or, for the fused designs, chunks {0, ntiles}.
 int build_graph(Common &c, int k, int par, bool batch, const Member &m,
                 const Member *d_members, const Tile *d_tiles,
                 const std::vector<int> &chunks, int grid,
-                const std::vector<BatchOp> *ops = nullptr, scmc_sim *sim = nullptr) {
+                scmc_batch *two_pass = nullptr, scmc_sim *sim = nullptr) {
     hipGraph_t g = nullptr;
     HIPCHK(c, hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
@@ -1018,51 +1058,10 @@ int build_graph(Common &c, int k, int par, bool batch, const Member &m,
         return SCMC_OK;
     };
     int cur = par, rc = SCMC_OK;
-    if (ops) {  // the two-pass launches of direct_steps_batch: chunk by chunk, k steps each
-        NodeLaunch dn{}, sn{}, dna{};
-        if (!node_batch_two_pass(c.key, 1, &dn, &sn, &dna))
-            rc = fail(c, SCMC_EUNSUPPORTED, "no graph node for this kernel");
-        const Member *dm = d_members;
-        const Tile *dt = d_tiles;
-        int nt = 0;
-        const void *srcv = nullptr;
-        void *dstv = nullptr;
-        void *densv = c.dens;
-        std::vector<void *> dargs = {(void *)&dm, (void *)&dt, (void *)&nt, (void *)&srcv,
-                                     (void *)&densv};
-        std::vector<void *> sargs = {(void *)&dm, (void *)&dt, (void *)&nt, (void *)&srcv,
-                                     (void *)&dstv, (void *)&densv};
-        for (size_t j = 0; !rc && j + 1 < ops->size(); j += 2)
-            for (int t = 0; !rc && t < k; ++t) {
-                const int cu = par ^ (t & 1);
-                srcv = c.pop[cu];
-                dstv = c.pop[1 - cu];
-                for (size_t q = j; !rc && q < j + 2; ++q) {
-                    const BatchOp &o = (*ops)[q];
-                    if (o.member >= 0) {  // a chunk of one member, as a single lattice
-                        NodeLaunch ml{};
-                        if (!node_member_pass(c.key, o.m, o.pass, o.nt_all, &ml)) {
-                            rc = fail(c, SCMC_EUNSUPPORTED, "no graph node for a member pass");
-                            break;
-                        }
-                        Member mv = o.m;
-                        std::vector<void *> margs = {(void *)&mv, (void *)&srcv};
-                        if (o.pass == 2) margs.push_back((void *)&dstv);
-                        margs.push_back((void *)&densv);
-                        rc = add(ml, margs);
-                        continue;
-                    }
-                    dt = d_tiles + o.t0;
-                    nt = o.n;
-                    NodeLaunch nl = o.pass == 1 ? (o.nt_all ? dna : dn) : sn;
-                    nl.grid = dim3(nt);  // one workgroup per tile
-                    rc = add(nl, o.pass == 1 ? dargs : sargs);
-                }
-            }
-    }
+    if (two_pass) rc = batch_steps(two_pass, k, par, add);
     const bool mom = sim && k >= 2 && mom_steps_on(sim);
     if (mom) rc = mom_steps(sim, k, par, add);
-    for (int t = 0; !ops && !mom && t < k && !rc; ++t) {
+    for (int t = 0; !two_pass && !mom && t < k && !rc; ++t) {
         for (size_t ch = 0; ch + 1 < chunks.size() && !rc; ++ch) {
             const int ntiles = chunks[ch + 1] - chunks[ch];
             // persistent fused launches: at most `grid` workgroups (clamped to
@@ -1684,6 +1683,13 @@ int scmc_flat_equilibrium(const scmc_problem *p, int lx, const double *guess,
 // their given order, until a chunk's moment fields would pass
 // kBatchChunkBytes.
 static constexpr size_t kBatchChunkBytes = (size_t)48 << 20;
+// Chunks that together have at most this much make their moment steps in one
+// launch: both fields of its members then stay in the Infinity Cache.  Longer
+// launches fill the CUs more evenly and march longer chunks: us per step of
+// twelve members of 48^3 to 88^3 (one group from 91 MB on) and of 48 members
+// of 48^3 to 160^3, by MB per group: 48: 164, 2 526; 112: 145, 2 416; 224:
+// 145, 2 435.  The two passes of every step took 271 and 5 190.
+static constexpr size_t kBatchGroupBytes = (size_t)112 << 20;
 
 static std::vector<std::vector<int>> two_pass_chunks(const std::vector<scmc_problem> &ps) {
     std::vector<std::vector<int>> out;
@@ -1740,7 +1746,9 @@ static int batch_tiles(const std::vector<scmc_problem> &ps, int kernel,
 static void batch_set_ops(scmc_batch *b) {
     const Common &c = b->c;
     b->ops.clear();
+    b->groups.clear();
     if (c.kernel == SCMC_KERNEL_FUSED) return;
+    std::vector<std::vector<int>> members_of;  // by chunk
     bool chunked = c.key.mom;
     for (const Lat &L : b->lats) chunked = chunked && !L.m.sr;
     std::vector<BatchOp> ops;
@@ -1748,7 +1756,8 @@ static void batch_set_ops(scmc_batch *b) {
         std::vector<scmc_problem> ps;
         for (const Lat &L : b->lats) ps.push_back(L.p);
         int t = 0;
-        for (const std::vector<int> &chunk : two_pass_chunks(ps)) {
+        members_of = two_pass_chunks(ps);
+        for (const std::vector<int> &chunk : members_of) {
             int n = 0;
             long sites = 0;
             for (int i : chunk) {
@@ -1766,10 +1775,37 @@ static void batch_set_ops(scmc_batch *b) {
             ops.push_back(p2);
             t += n;
         }
-        if (t != b->ntiles) ops.clear();
+        if (t != b->ntiles) {
+            ops.clear();
+            members_of.clear();
+        }
     }
     if (ops.empty()) ops = {{1, 0, b->ntiles}, {2, 0, b->ntiles}};
     b->ops = ops;
+    if (members_of.size() * 2 != ops.size()) {  // the whole list, not by chunks
+        b->groups.push_back(BatchGroup{0, ops.size(), 0});
+        return;
+    }
+    // groups of consecutive chunks that share a moment step's launch
+    for (size_t q = 0; q < members_of.size();) {
+        BatchGroup g;
+        g.op0 = 2 * q;
+        g.member = members_of[q][0];
+        std::vector<Member> ms;
+        size_t bytes = 0;
+        for (; q < members_of.size(); ++q) {
+            size_t more = 0;
+            for (int i : members_of[q]) more += (size_t)6 * b->lats[i].m.N * real_bytes(b->lats[i].p.storage);
+            if (!ms.empty() && (bytes + more > kBatchGroupBytes ||
+                                ms.size() + members_of[q].size() > (size_t)MOM_LIST))
+                break;
+            bytes += more;
+            for (int i : members_of[q]) ms.push_back(b->lats[i].m);
+        }
+        g.op1 = 2 * q;
+        g.mom = node_batch_mom_step(c.key, ms, g.member, &g.node, &g.list);
+        b->groups.push_back(g);
+    }
 }
 
 // Tile-list capacity: enough for the current design, for the smallest fused
@@ -1950,7 +1986,7 @@ int scmc_batch_step(scmc_batch *b, int64_t nsteps) {
             const std::vector<int> whole = {0, b->ntiles};
             return build_graph(c, c.graph_k, par, true, Member{}, b->d_members, b->d_tiles,
                                whole, b->grid,
-                               c.kernel == SCMC_KERNEL_FUSED ? nullptr : &b->ops);
+                               c.kernel == SCMC_KERNEL_FUSED ? nullptr : b);
         },
         [&](int64_t k) { return direct_steps_batch(b, k); });
 }

@@ -82,14 +82,6 @@ bool fused_supported(const StepKey &k, const int *tile);
 // start only after others had run their whole share of the list.  (The
 // two-pass batched launches run one workgroup per 256-site tile.)
 int resident_blocks(const void *f, int threads, unsigned shmem = 0);
-// grid: workgroups; one per tile runs each tile once.  passes: 1 = pass 1
-// only, 2 = pass 2 only, 3 = both.  nt_all: pass 1 loads every population
-// non-temporally (FP32 moment two-pass; see pass1_nt_all)
-hipError_t launch_batch_two_pass(const StepKey &k, const Member *d_members,
-                                 const Tile *d_tiles, int ntiles,
-                                 const void *src, void *dst, void *dens,
-                                 int grid, hipStream_t st, int passes = 3,
-                                 bool nt_all = false);
 // Whether pass 1 of the moment two-pass over `sites` sites (one unslabbed
 // lattice, or one chunk of a batch) loads every population non-temporally.
 bool pass1_nt_all(const StepKey &k, long sites);
@@ -127,14 +119,12 @@ bool node_fused(const StepKey &k, const int *tile, NodeLaunch *node,
 // launched like a single lattice (linear 256-site blocks, the member's
 // description a kernel argument instead of a per-block load from the tile
 // list).  D3Q19 buffer forms without node storage or stochastic rounding;
-// node_member_pass returns false (launch_member_pass hipErrorNotSupported)
-// for every other key.  nt_all as in launch_batch_two_pass.
+// returns false for every other key.  nt_all as in pass1_nt_all.
 bool node_member_pass(const StepKey &k, const Member &m, int pass, bool nt_all,
                       NodeLaunch *node);
-hipError_t launch_member_pass(const StepKey &k, const Member &m, const void *src, void *dst,
-                              void *dens, int pass, bool nt_all, hipStream_t st);
-// dens_node_nt_all (optional): the pass-1 node of launch_batch_two_pass's
-// nt_all form (the same as dens_node where there is none)
+// The batched two-pass: one workgroup per tile of a tile list.
+// dens_node_nt_all (optional): the pass-1 node with every load non-temporal
+// (the same as dens_node where there is none).
 bool node_batch_two_pass(const StepKey &k, int grid, NodeLaunch *dens_node,
                          NodeLaunch *step_node, NodeLaunch *dens_node_nt_all = nullptr);
 bool node_batch_fused(const StepKey &k, const int *tile, int grid,
@@ -151,6 +141,21 @@ struct MomShape {
 // key.  Kernel arguments: Member, MomShape, const void *in, void *out (moment
 // fields), int in_slot, int out_slot (slots of their (n_A, n_B) pairs).
 bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape);
+// The same for consecutive members of a batch in one launch: block b works on
+// the last entry whose first block is <= b, which its lanes find by one load
+// each, so a list has at most one entry per lane.
+constexpr int MOM_LIST = 64;
+struct MomList {
+    int n;
+    struct Entry {
+        int first, member;
+        MomShape g;
+    } e[MOM_LIST];
+};
+// Kernel arguments: const Member *, MomList, const void *in, void *out (the
+// moment fields' base, to which each member's dens_off is added).
+bool node_batch_mom_step(const StepKey &k, const std::vector<Member> &ms, int first_member,
+                         NodeLaunch *node, MomList *list);
 
 // ---- steps of a lattice uniform along y and z (row_kernels.hip)
 bool row_steps_supported(const StepKey &k, const Member &m);

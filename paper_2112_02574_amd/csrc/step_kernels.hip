@@ -845,77 +845,6 @@ int resident_blocks(const void *f, int threads, unsigned shmem) {
     return cache[key] = per * ncu;
 }
 
-hipError_t launch_batch_two_pass(const StepKey &k, const Member *d_members,
-                                 const Tile *d_tiles, int ntiles,
-                                 const void *src, void *dst, void *dens,
-                                 int grid, hipStream_t st, int passes, bool nt_all) {
-    const bool p1 = passes & 1, p2 = passes & 2;
-    hipError_t err = hipErrorInvalidValue;
-    dispatch_storage(k.storage, [&](auto stv) {
-        using ST = decltype(stv);
-        using T = typename ST::T;
-        using R = typename ST::R;
-        dispatch_shape<ST>(k, [&](auto Dc, auto Oc, auto Pc) {
-            constexpr int D = decltype(Dc)::value;
-            constexpr int O = decltype(Oc)::value;
-            constexpr int P = decltype(Pc)::value;
-            const dim3 b(TP_BX, TP_BY, 1);
-            bool done = false;
-            if constexpr (buf_form<D, ST>()) {
-                if (k.mom && !k.big) {
-                    bool all = false;
-                    if constexpr (nt_all_form<ST, false>()) all = nt_all;
-                    if (p1 && all)
-                        hipLaunchKernelGGL((kb_moments_buf<ST, PULL_NT_ALL>), dim3(grid), b, 0, st,
-                                           d_members, d_tiles, ntiles, (const T *)src,
-                                           (R *)dens);
-                    else if (p1)
-                        hipLaunchKernelGGL((kb_moments_buf<ST>), dim3(grid), b, 0, st,
-                                           d_members, d_tiles, ntiles, (const T *)src,
-                                           (R *)dens);
-                    if (p2 && k.sr) {
-                        if constexpr (!sr_form<ST>()) {
-                            err = hipErrorNotSupported;
-                            return;
-                        } else {
-                            hipLaunchKernelGGL((kb_collide_mom_buf<O, ST, P, true>), dim3(grid), b,
-                                               0, st, d_members, d_tiles, ntiles, (const T *)src,
-                                               (T *)dst, (const R *)dens);
-                        }
-                    } else if (p2) {
-                        hipLaunchKernelGGL((kb_collide_mom_buf<O, ST, P>), dim3(grid), b, 0,
-                                           st, d_members, d_tiles, ntiles, (const T *)src,
-                                           (T *)dst, (const R *)dens);
-                    }
-                    done = true;
-                }
-            }
-            if (done) {
-            } else if (k.mom) {
-                if (p1)
-                    hipLaunchKernelGGL((kb_moments<D, ST>), dim3(grid), b, 0, st,
-                                       d_members, d_tiles, ntiles, (const T *)src,
-                                       (R *)dens);
-                if (p2)
-                    hipLaunchKernelGGL((kb_collide_mom<D, O, ST, P>), dim3(grid), b, 0,
-                                       st, d_members, d_tiles, ntiles, (const T *)src,
-                                       (T *)dst, (const R *)dens);
-            } else {
-                if (p1)
-                    hipLaunchKernelGGL((kb_density<D, ST>), dim3(grid), b, 0, st,
-                                       d_members, d_tiles, ntiles, (const T *)src,
-                                       (R *)dens);
-                if (p2)
-                    hipLaunchKernelGGL((kb_collide<D, O, ST, P>), dim3(grid), b, 0,
-                                       st, d_members, d_tiles, ntiles, (const T *)src,
-                                       (T *)dst, (const R *)dens);
-            }
-            err = hipGetLastError();
-        });
-    });
-    return err;
-}
-
 bool node_member_pass(const StepKey &k, const Member &m, int pass, bool nt_all,
                       NodeLaunch *nl) {
     bool ok = false;
@@ -943,18 +872,6 @@ bool node_member_pass(const StepKey &k, const Member &m, int pass, bool nt_all,
         });
     });
     return ok;
-}
-
-hipError_t launch_member_pass(const StepKey &k, const Member &m, const void *src, void *dst,
-                              void *dens, int pass, bool nt_all, hipStream_t st) {
-    NodeLaunch nl{};
-    if (!node_member_pass(k, m, pass, nt_all, &nl)) return hipErrorNotSupported;
-    Member mv = m;
-    const void *srcv = src;
-    void *dstv = dst, *densv = dens;
-    void *a1[] = {(void *)&mv, (void *)&srcv, (void *)&densv};
-    void *a2[] = {(void *)&mv, (void *)&srcv, (void *)&dstv, (void *)&densv};
-    return hipLaunchKernel(nl.func, nl.grid, nl.block, pass == 1 ? a1 : a2, 0, st);
 }
 
 bool node_batch_two_pass(const StepKey &k, int grid, NodeLaunch *dn,

@@ -81,3 +81,34 @@ def test_block_large_lattice_equals_single_steps():
         f1, _ = _run(p, st, [1] * 3)
         f3, _ = _run(p, st, [3])
         assert np.array_equal(f3, f1)
+
+
+def _batch_equals_singles(shapes, storage, calls, stencil=6, graph=0):
+    ps = [_problem(s, stencil, storage) for s in shapes]
+    b = scmc.Batch(ps)
+    for i, s in enumerate(shapes):
+        b.scmc_batch_set_density(i, *_state(s, seed=7 + i))
+    if graph:
+        b.scmc_batch_set_graph_steps(graph)
+    for k in calls:
+        b.scmc_batch_step(k)
+    for i, s in enumerate(shapes):
+        _, n = _run(ps[i], _state(s, seed=7 + i), [1] * sum(calls))
+        assert np.array_equal(b.scmc_batch_get_fields(i), n), (i, s)
+    b.close()
+
+
+@pytest.mark.parametrize("storage", [scmc.F64, scmc.F32, scmc.F16_OFF])
+@pytest.mark.parametrize("graph", [0, 2])
+def test_batch_block_equals_single_steps(storage, graph):
+    """Ragged members in one launch; odd and even blocks from both buffers."""
+    _batch_equals_singles([(5, 5, 5), (24, 31, 40), (33, 20, 70), (9, 9, 100)], storage, [3, 4], graph=graph)
+    _batch_equals_singles([(3, 3, 3), (12, 40, 7)], storage, [5], stencil=4, graph=graph)
+
+
+def test_batch_groups_equal_single_steps():
+    """Members beyond one group (112 MB of moments, 64 members): the second
+    field of a group lies in its own part of the other population buffer."""
+    _batch_equals_singles([(128, 128, 130), (128, 128, 128), (90, 128, 128), (20, 20, 20)],
+                          scmc.F16_OFF, [3])
+    _batch_equals_singles([(5 + i % 3, 6, 7) for i in range(70)], scmc.F32, [3])
