@@ -18,6 +18,7 @@ LIB = os.path.join(HERE, "libscmc.so")
 SOURCES = [("step_kernels.hip", "step_kernels", []),
            ("fused_kernels.hip", "fused_kernels", []),
            ("moment_kernels.hip", "moment_kernels", []),
+           ("moment2d_kernels.hip", "moment2d_kernels", []),
            ("row_kernels.hip", "row_kernels", []),
            ("obs_kernels.hip", "obs_kernels", []),
            ("ceiling_kernels.hip", "ceiling_kernels", []),

@@ -100,7 +100,7 @@ static MomKernel mom_kernel(const StepKey &k) {
     return f;
 }
 
-static int compute_units() {
+int compute_units() {
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||

@@ -210,6 +210,7 @@ struct scmc_sim {
     bool mom_ok = false;  // blocks of steps can stay in the moment field
     NodeLaunch mom_node{};
     MomShape mom_shape{};
+    int mom2 = 0;  // D2Q9: the most steps that a launch of mom_node makes
     bool have_prev = false;  // convergence monitor: a previous check exists
     double prev_dP = 0;
     int64_t prev_step = 0;
@@ -881,11 +882,12 @@ bool mom_steps_on(const scmc_sim *s) {
 }
 
 // The launches of k >= 2 steps from buffer par that stay in the moment field:
-// pass 1, k - 1 moment steps, pass 2; each goes to emit(launch, arguments).
+// pass 1, k - 1 moment steps (2D: several per launch), pass 2; each goes to
+// emit(launch, arguments).
 // The moments alternate between the workspace's moment field, where the last
 // ones must be for pass 2, and the population buffer that pass 1 does not
 // read, whose contents no one needs any more and pass 2 at most overwrites
-// (24 or 48 B per site of its 76 to 304).  Node storage keeps the last pairs
+// (24 or 48 B per site of its 36 to 304).  Node storage keeps the last pairs
 // as the reference field of the buffer that pass 2 fills.
 template <class Emit>
 int mom_steps(scmc_sim *s, int64_t k, int par, Emit &&emit) {
@@ -900,7 +902,10 @@ int mom_steps(scmc_sim *s, int64_t k, int par, Emit &&emit) {
     Member m1 = step_member(c, m, par), m2 = step_member(c, m, last);
     void *field[2] = {c.dens, c.pop[1 - par]};
     const int slot[2] = {m2.pair_slot, 0};
-    int at = (int)((k - 1) & 1);  // the field that holds the current moments
+    // one moment step per launch in 3D; in 2D launches of equal numbers of
+    // steps, at most mom2
+    const int64_t nl = s->mom2 ? (k - 2 + s->mom2) / s->mom2 : k - 1;
+    int at = (int)(nl & 1);  // the field that holds the current moments
     m1.pair_slot = slot[at];
     const void *src = c.pop[par], *src2 = c.pop[last];
     void *dst = c.pop[1 - last];
@@ -908,10 +913,17 @@ int mom_steps(scmc_sim *s, int64_t k, int par, Emit &&emit) {
     int rc = emit(p1, a1);
     Member ms = m;
     MomShape shape = s->mom_shape;
-    for (int64_t t = 1; t < k && !rc; ++t, at ^= 1) {
+    for (int64_t t = 0; t < nl && !rc; ++t, at ^= 1) {
         int si = slot[at], so = slot[1 - at];
-        std::vector<void *> a = {(void *)&ms, (void *)&shape, (void *)&field[at],
-                                 (void *)&field[1 - at], (void *)&si, (void *)&so};
+        int steps = (int)((k - 1) / nl + (t < (k - 1) % nl ? 1 : 0));
+        std::vector<void *> a = {(void *)&ms, (void *)&shape};
+        if (s->mom2) a.push_back((void *)&steps);
+        a.push_back((void *)&field[at]);
+        a.push_back((void *)&field[1 - at]);
+        if (!s->mom2) {
+            a.push_back((void *)&si);
+            a.push_back((void *)&so);
+        }
         rc = emit(s->mom_node, a);
     }
     std::vector<void *> a2 = {(void *)&m2, (void *)&src2, (void *)&dst, (void *)&field[0]};
@@ -1244,7 +1256,9 @@ int scmc_create(const scmc_problem *p, void *d_ws, size_t ws_bytes,
     c.ws_bytes = ws_bytes;
     bind(c, pl, c.ws, stats_blocks(s->lat.m));
     s->lat.m.step_ctr = c.ctr;
-    s->mom_ok = node_mom_step(c.key, s->lat.m, &s->mom_node, &s->mom_shape);
+    s->mom_ok = s->lat.dim == 3
+                    ? node_mom_step(c.key, s->lat.m, &s->mom_node, &s->mom_shape)
+                    : node_mom2_steps(c.key, s->lat.m, &s->mom_node, &s->mom_shape, &s->mom2);
     *out = s;
     return SCMC_OK;
 }

@@ -141,7 +141,12 @@ struct MomShape {
 // key.  Kernel arguments: Member, MomShape, const void *in, void *out (moment
 // fields), int in_slot, int out_slot (slots of their (n_A, n_B) pairs).
 bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape);
-// The same for consecutive members of a batch in one launch: block b works on
+int compute_units();  // of the current device (256 where it cannot be asked)
+// D2Q9 (moment2d_kernels.hip): up to *steps steps per launch.  Kernel
+// arguments: Member, MomShape, int steps, const void *in, void *out.
+bool node_mom2_steps(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape,
+                     int *steps);
+// node_mom_step for consecutive members of a batch in one launch: block b works on
 // the last entry whose first block is <= b, which its lanes find by one load
 // each, so a list has at most one entry per lane.
 constexpr int MOM_LIST = 64;

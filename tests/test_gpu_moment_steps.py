@@ -112,3 +112,26 @@ def test_batch_groups_equal_single_steps():
     _batch_equals_singles([(128, 128, 130), (128, 128, 128), (90, 128, 128), (20, 20, 20)],
                           scmc.F16_OFF, [3])
     _batch_equals_singles([(5 + i % 3, 6, 7) for i in range(70)], scmc.F32, [3])
+
+
+SHAPES_2D = {4: [(3, 3), (4, 70), (64, 64), (33, 130)], 6: [(5, 5), (64, 7), (61, 67)],
+             8: [(5, 6), (40, 41), (200, 257)]}
+
+
+@pytest.mark.parametrize("storage", [scmc.F64, scmc.F32, scmc.F16_OFF, scmc.BF16_OFF])
+@pytest.mark.parametrize("stencil", [4, 6, 8])
+@pytest.mark.parametrize("psi,g", [(scmc.PSI_N, ASYM), (scmc.PSI_EXP_NEG_INV, PAPER)])
+def test_block_2d_equals_single_steps(storage, stencil, psi, g):
+    """Blocks shorter and longer than a launch's steps, direct and in graphs."""
+    for shape in SHAPES_2D[stencil]:
+        p = scmc.problem(scmc.D2Q9, stencil, shape, g=g, psi_self=psi, storage=storage)
+        nA, nB = inputs.droplet(shape[1], shape[0], R=max(2.0, min(shape) / 4))
+        noise = [1 + 1e-3 * (2 * inputs.splitmix64_uniform_array(3 + t, nA.size) - 1).reshape(nA.shape)
+                 for t in range(2)]
+        st = (nA * noise[0], nB * noise[1])
+        f1, n1 = _run(p, st, [1] * 21)
+        f2, n2 = _run(p, st, [2, 19])
+        np.testing.assert_array_equal(f2, f1, err_msg=str(shape))
+        np.testing.assert_array_equal(n2, n1, err_msg=str(shape))
+        f3, _ = _run(p, st, [14, 7], graph=5)
+        np.testing.assert_array_equal(f3, f1, err_msg=str(shape))
