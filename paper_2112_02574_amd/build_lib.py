@@ -19,6 +19,7 @@ SOURCES = [("step_kernels.hip", "step_kernels", []),
            ("fused_kernels.hip", "fused_kernels", []),
            ("moment_kernels.hip", "moment_kernels", []),
            ("moment2d_kernels.hip", "moment2d_kernels", []),
+           ("once_kernels.hip", "once_kernels", []),
            ("row_kernels.hip", "row_kernels", []),
            ("obs_kernels.hip", "obs_kernels", []),
            ("ceiling_kernels.hip", "ceiling_kernels", []),

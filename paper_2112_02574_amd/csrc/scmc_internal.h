@@ -162,6 +162,12 @@ struct MomList {
 bool node_batch_mom_step(const StepKey &k, const std::vector<Member> &ms, int first_member,
                          NodeLaunch *node, MomList *list);
 
+// ---- one step of a small lattice in one launch (once_kernels.hip): whether m
+// takes it, and the boxes; launch_two_pass asks for it by itself
+bool step_once_shape(const StepKey &k, const Member &m, MomShape *g);
+hipError_t launch_step_once(const StepKey &k, const Member &m, const MomShape &g, const void *src,
+                            void *dst, hipStream_t st);
+
 // ---- steps of a lattice uniform along y and z (row_kernels.hip)
 bool row_steps_supported(const StepKey &k, const Member &m);
 // nsteps >= 1 steps from src; dst (may be src) gets the whole lattice's state

@@ -660,6 +660,8 @@ std::vector<SlabOp> slab_schedule(const StepKey &k, const Member &m) {
 
 hipError_t launch_two_pass(const StepKey &k, const Member &m, const void *src,
                            void *dst, void *dens, hipStream_t st) {
+    MomShape boxes;
+    if (step_once_shape(k, m, &boxes)) return launch_step_once(k, m, boxes, src, dst, st);
     hipError_t err = hipErrorInvalidValue;
     dispatch_storage(k.storage, [&](auto stv) {
         using ST = decltype(stv);
