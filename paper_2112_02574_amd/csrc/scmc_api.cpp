@@ -764,10 +764,11 @@ int fields_impl(Common &c, const Lat &L, const void *pop_base, double *nA,
     const size_t N = (size_t)m.N;
     int rc = member_obs_prep(c, L, pop_base);
     if (rc) return rc;
+    const bool both = nA && nB == nA + N;  // one array: one copy
     if (nA)
-        HIPCHK(c, hipMemcpyAsync(nA, c.dens64, N * 8, hipMemcpyDeviceToHost,
+        HIPCHK(c, hipMemcpyAsync(nA, c.dens64, (both ? 2 : 1) * N * 8, hipMemcpyDeviceToHost,
                                  c.stream));
-    if (nB)
+    if (nB && !both)
         HIPCHK(c, hipMemcpyAsync(nB, c.dens64 + N, N * 8,
                                  hipMemcpyDeviceToHost, c.stream));
     if (u) {

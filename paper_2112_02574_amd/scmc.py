@@ -351,11 +351,9 @@ class Sim:
         self._check(lib().scmc_synchronize(self.h), "scmc_synchronize")
 
     def scmc_get_fields(self, velocity=False):
-        nA = np.zeros(self.N)
-        nB = np.zeros(self.N)
+        n = np.empty((2,) + self.shape)  # filled in place, one copy from the device
         u = np.zeros(3 * self.N) if velocity else None
-        self._check(lib().scmc_get_fields(self.h, _ptr(nA), _ptr(nB), _ptr(u)), "scmc_get_fields")
-        n = np.stack([nA, nB]).reshape((2,) + self.shape)
+        self._check(lib().scmc_get_fields(self.h, _ptr(n[0]), _ptr(n[1]), _ptr(u)), "scmc_get_fields")
         return (n, u.reshape((3,) + self.shape)) if velocity else n
 
     def scmc_get_populations(self):
@@ -473,11 +471,10 @@ class Batch:
 
     def scmc_batch_get_fields(self, i, velocity=False):
         N, shp = self._n(i)
-        nA, nB = np.zeros(N), np.zeros(N)
+        n = np.empty((2,) + shp)
         u = np.zeros(3 * N) if velocity else None
-        self._check(lib().scmc_batch_get_fields(self.h, i, _ptr(nA), _ptr(nB), _ptr(u)),
+        self._check(lib().scmc_batch_get_fields(self.h, i, _ptr(n[0]), _ptr(n[1]), _ptr(u)),
                     "scmc_batch_get_fields")
-        n = np.stack([nA, nB]).reshape((2,) + shp)
         return (n, u.reshape((3,) + shp)) if velocity else n
 
     def scmc_batch_get_populations(self, i):
