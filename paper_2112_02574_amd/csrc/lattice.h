@@ -132,23 +132,18 @@ template <int D, int ORDER> struct Stencil {
 };
 
 // ----------------------------------------------------------- storage formats
-// load(p, i, ref) returns the population in compute precision; ref = w_i n0_J
-// is the offset reference (used by the FP16 / BF16 offset formats only).
-// Stores are non-temporal: every population is written once per step and
-// only read again by the next step, after the whole buffer has streamed.
+// encode(v, w, n0) and decode(h, w, n0) convert a population; w_i n0_J is the
+// offset reference (used by the FP16 / BF16 offset formats only).  to_raw_sr
+// rounds stochastically, against ref = w_i n0_J.  The two-pass kernels store
+// non-temporally: every population is written once per step and only read
+// again by the next step, after the whole buffer has streamed.
 struct StoreF64 {
     using T = double;
     using R = double;
     static constexpr int BYTES = 8;
-    __device__ __forceinline__ static R from_raw(T v, R) { return v; }
-    __device__ __forceinline__ static T to_raw(R v, R) { return v; }
     __device__ __forceinline__ static T encode(R v, R, R) { return v; }
     __device__ __forceinline__ static R decode(T v, R, R) { return v; }
     __device__ __forceinline__ static R stored(R v, R, R) { return v; }
-    __device__ __forceinline__ static R load(const T *p, long i, R) { return p[i]; }
-    __device__ __forceinline__ static void store(T *p, long i, R v, R) {
-        __builtin_nontemporal_store(v, p + i);
-    }
     __device__ __forceinline__ static T to_raw_sr(R v, R, unsigned) { return v; }
 };
 
@@ -156,15 +151,9 @@ struct StoreF32 {
     using T = float;
     using R = float;
     static constexpr int BYTES = 4;
-    __device__ __forceinline__ static R from_raw(T v, R) { return v; }
-    __device__ __forceinline__ static T to_raw(R v, R) { return v; }
     __device__ __forceinline__ static T encode(R v, R, R) { return v; }
     __device__ __forceinline__ static R decode(T v, R, R) { return v; }
     __device__ __forceinline__ static R stored(R v, R, R) { return v; }
-    __device__ __forceinline__ static R load(const T *p, long i, R) { return p[i]; }
-    __device__ __forceinline__ static void store(T *p, long i, R v, R) {
-        __builtin_nontemporal_store(v, p + i);
-    }
     __device__ __forceinline__ static T to_raw_sr(R v, R, unsigned) { return v; }
 };
 
@@ -172,22 +161,8 @@ struct StoreF16 {
     using T = uint16_t;
     using R = float;
     static constexpr int BYTES = 2;
-    __device__ __forceinline__ static R from_raw(T v, R ref) {
-        return __half2float(__ushort_as_half(v)) + ref;
-    }
-    __device__ __forceinline__ static T to_raw(R v, R ref) {
-        return __half_as_ushort(__float2half_rn(v - ref));
-    }
-    __device__ __forceinline__ static R load(const T *p, long i, R ref) {
-        return __half2float(__ushort_as_half(p[i])) + ref;
-    }
-    __device__ __forceinline__ static void store(T *p, long i, R v, R ref) {
-        const T h = __half_as_ushort(__float2half_rn(v - ref));
-        __builtin_nontemporal_store(h, p + i);
-    }
-    // encode / decode: to_raw / from_raw with the reference w n0 inside both
-    // roundings, as the compiler contracts them around the product in the two
-    // passes; stored: the value that a load finds of a stored one
+    // the product w n0 inside both roundings (one fused multiply-add each);
+    // stored: the value that a load finds of a stored one
     __device__ __forceinline__ static T encode(R v, R w, R n0) {
         return __half_as_ushort(__float2half_rn(__builtin_fmaf(-w, n0, v)));
     }
@@ -214,7 +189,8 @@ struct StoreF16 {
     // rounded to nearest, their absolute error being below 2^-25.
     __device__ __forceinline__ static T to_raw_sr(R v, R ref, unsigned r) {
         const float x = v - ref;
-        if (!(fabsf(x) >= 6.103515625e-05f) || fabsf(x) > 6.5e4f) return to_raw(v, ref);
+        if (!(fabsf(x) >= 6.103515625e-05f) || fabsf(x) > 6.5e4f)
+            return __half_as_ushort(__float2half_rn(x));
         const unsigned u = __float_as_uint(x) + (r & 0x1FFFu);
         return __half_as_ushort(__float2half_rz(__uint_as_float(u)));
     }
@@ -248,19 +224,6 @@ struct StoreBF16 {
     using T = uint16_t;
     using R = float;
     static constexpr int BYTES = 2;
-    __device__ __forceinline__ static R from_raw(T v, R ref) {
-        return bf16_to_f32(v) + ref;
-    }
-    __device__ __forceinline__ static T to_raw(R v, R ref) {
-        return f32_to_bf16_dev(v - ref);
-    }
-    __device__ __forceinline__ static R load(const T *p, long i, R ref) {
-        return bf16_to_f32(p[i]) + ref;
-    }
-    __device__ __forceinline__ static void store(T *p, long i, R v, R ref) {
-        const T h = f32_to_bf16_dev(v - ref);
-        __builtin_nontemporal_store(h, p + i);
-    }
     __device__ __forceinline__ static T encode(R v, R w, R n0) {  // as in StoreF16
         return f32_to_bf16_dev(__builtin_fmaf(-w, n0, v));
     }
@@ -271,8 +234,10 @@ struct StoreBF16 {
         return decode(encode(v, w, n0), w, n0);
     }
     // node storage: bfloat16 has the binary32 exponent range, no scale
-    __device__ __forceinline__ static T to_node(R v, R ref) { return to_raw(v, ref); }
-    __device__ __forceinline__ static R from_node(T v, R ref) { return from_raw(v, ref); }
+    __device__ __forceinline__ static T to_node(R v, R ref) {
+        return f32_to_bf16_dev(v - ref);
+    }
+    __device__ __forceinline__ static R from_node(T v, R ref) { return bf16_to_f32(v) + ref; }
     // Stochastic rounding: 16 random bits added below the kept half of the
     // binary32 pattern, then truncation (sign-magnitude: unbiased for both
     // signs); infinities and NaN go the nearest-even way.

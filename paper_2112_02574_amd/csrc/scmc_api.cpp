@@ -406,10 +406,14 @@ Member member_of(const scmc_problem &p) {
 int choose_kernel(const scmc_problem &p, const StepKey &k, int *kernel,
                   int *tile) {
     int t[3] = {p.tile[0], p.tile[1], p.tile[2]};
-    // at tau = 1 the default is the moment two-pass design (the fastest
-    // untuned choice on a 128^3 sweep); the autotuner may pick a fused one
+    // the default is the moment two-pass design at tau = 1 and the any-tau two
+    // passes otherwise, the fastest untuned choices: us per step at tau = 0.8,
+    // E6, against the fused design's default tile (64, 8, 16), 64^3 FP32 25
+    // against 120, 128^3 FP32 192 against 203, FP16 101 against 133,
+    // 160 x 150 x 155 FP32 345 against 591.  The autotuner may pick a fused one
+    // (128^3 FP32 with (128, 4, 16): 181).
     if (k.node || p.kernel == SCMC_KERNEL_TWO_PASS || p.kernel == SCMC_KERNEL_TWO_PASS_MOM ||
-        (p.kernel == SCMC_KERNEL_AUTO && k.mom && t[0] == 0) ||
+        (p.kernel == SCMC_KERNEL_AUTO && t[0] == 0) ||
         (p.kernel == SCMC_KERNEL_AUTO && p.rounding == SCMC_ROUND_STOCHASTIC)) {
         *kernel = SCMC_KERNEL_TWO_PASS;
         const bool lds = k.mom == 2;
@@ -2065,7 +2069,8 @@ struct Candidate {
 // Designs this problem can run: for kernel AUTO the population-ring fused
 // designs (plain and pipelined) over the compiled tiles and three z-chunk
 // lengths and, at tau = 1, the moment-ring fused designs and the moment
-// two-pass design; for a fixed fused design, its tiles only.
+// two-pass design, otherwise the any-tau two passes; for a fixed fused design,
+// its tiles only.
 std::vector<Candidate> candidates(const scmc_problem &p, const StepKey &k0, int nx) {
     static const int tiles[][2] = {{64, 4}, {32, 8},  {64, 8}, {32, 16},
                                    {128, 4}, {128, 8}, {64, 16}};
@@ -2097,6 +2102,8 @@ std::vector<Candidate> candidates(const scmc_problem &p, const StepKey &k0, int 
                 if (fused_supported(k, c.tile)) out.push_back(c);
             }
         }
+    if (p.kernel == SCMC_KERNEL_AUTO && !tau1 && k0.dim == 3)
+        out.push_back(Candidate{SCMC_KERNEL_TWO_PASS, 0, 0, {0, 0, 0}});
     if (p.kernel == SCMC_KERNEL_AUTO && tau1) {
         out.push_back(Candidate{SCMC_KERNEL_TWO_PASS, 0, 1, {0, 0, 0}});
         if (k0.dim == 3 && !k0.big && p.storage != SCMC_F64)  // LDS-staged collision pass

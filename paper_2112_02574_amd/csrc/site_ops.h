@@ -88,12 +88,12 @@ __device__ __forceinline__ void pull_site(
         const long s = ((long)zs * m.ny + ys) * m.nx + xs;
         const R w = (R)L::W[i];
         if (NT && L::CX[i] == 0) {
-            f[0][i] = ST::from_raw(__builtin_nontemporal_load(base + (long)i * m.N + s), w * n0A);
-            f[1][i] = ST::from_raw(__builtin_nontemporal_load(base + (long)(L::Q + i) * m.N + s),
-                                   w * n0B);
+            f[0][i] = ST::decode(__builtin_nontemporal_load(base + (long)i * m.N + s), w, n0A);
+            f[1][i] = ST::decode(__builtin_nontemporal_load(base + (long)(L::Q + i) * m.N + s), w,
+                                 n0B);
         } else {
-            f[0][i] = ST::load(base, (long)i * m.N + s, w * n0A);
-            f[1][i] = ST::load(base, (long)(L::Q + i) * m.N + s, w * n0B);
+            f[0][i] = ST::decode(base[(long)i * m.N + s], w, n0A);
+            f[1][i] = ST::decode(base[(long)(L::Q + i) * m.N + s], w, n0B);
         }
     }
 }
@@ -106,199 +106,7 @@ __device__ __forceinline__ void pull_site(
 // commutes bit for bit with the reflections: a droplet centred on a node
 // keeps its centre, which the convergence gate of Sec. 4 checks to 1e-3,
 // instead of being pushed by the same rounding bias every step.
-template <int D, class R>
-__device__ __forceinline__ void site_density(const R (&f)[2][Lattice<D>::Q],
-                                             R &nA, R &nB) {
-    double a = 0, b = 0;
-#pragma unroll
-    for (int i = 0; i < Lattice<D>::Q; ++i) {
-        a += (double)f[0][i];
-        b += (double)f[1][i];
-    }
-    nA = (R)a;
-    nB = (R)b;
-}
-
-// One component of the force: -g n_J c_K - g_JJ psi_J s_J (c, s: stencil sums)
-template <class R> __device__ __forceinline__ R sc_force(R g, R n, R c, R gs, R psi, R s) {
-#pragma clang fp contract(off)
-    const R self = gs * psi * s, gn = -g * n;
-    if constexpr (std::is_same<R, float>::value) return __builtin_fmaf(gn, c, -self);
-    else return __builtin_fma(gn, c, -self);
-}
-
-// Stencil sums of eq. sc_force around site (x, y, z), with the stencil
-// concentrations returned by fetch(t, n_A, n_B) (t = linear site index times
-// UNIT, e.g. a byte offset into an array of (n_A, n_B) pairs), then the force
-// on both components.  The stencil is point-symmetric, so the sum runs over
-// pairs (e, -e): W e (Phi(x + e) - Phi(x - e)).  The difference is exactly
-// odd under e -> -e and the pair sums are accumulated in FP64 (the order-free
-// sums above).
-template <int D, int ORDER, int PSI, class R, int UNIT = 1, class Fetch>
-__device__ __forceinline__ void site_force_fn(const Member &m, int x, int y, int z,
-                                              R nA, R nB, R (&FA)[3], R (&FB)[3],
-                                              Fetch &&fetch) {
-    using S = Stencil<D, ORDER>;
-    static_assert(S::point_symmetric(), "stencil table must list e and -e mirrored");
-    double cA[3] = {0, 0, 0}, cB[3] = {0, 0, 0};
-    double sA[3] = {0, 0, 0}, sB[3] = {0, 0, 0};
-    const bool selfA = m.self_on & 1, selfB = m.self_on & 2;
-    // periodic column, row and plane offsets of x + d, y + d, z + d for
-    // d = -2..2, formed once: a stencil neighbour is then two additions
-    int xo[5], yo[5], zo[5];
-#pragma unroll
-    for (int d = -2; d <= 2; ++d) {
-        xo[d + 2] = wrap1(x + d, m.nx) * UNIT;
-        yo[d + 2] = wrap1(y + d, m.ny) * (m.nx * UNIT);
-        zo[d + 2] = D == 3 ? wrap1(z + d, m.nz) * (m.nx * m.ny * UNIT) : 0;
-    }
-#pragma unroll
-    for (int a = S::NE / 2; a < S::NE; ++a) {
-        constexpr auto T = S::T;
-        const int ex = T.e[a][0], ey = T.e[a][1], ez = T.e[a][2];
-        const int tp = zo[2 + ez] + yo[2 + ey] + xo[2 + ex];
-        const int tm = zo[2 - ez] + yo[2 - ey] + xo[2 - ex];
-        R pAt, pBt, mAt, mBt;  // N * UNIT < 2^31 (the callers' forms)
-        fetch(tp, pAt, pBt);
-        fetch(tm, mAt, mBt);
-        const R dA = pAt - mAt, dB = pBt - mBt;
-        const R W = (R)T.W[a];
-        const int e3[3] = {ex, ey, ez};
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-            if (e3[k] == 0) continue;
-            const double We = (double)(W * (R)e3[k]);
-            cA[k] += We * (double)dB;
-            cB[k] += We * (double)dA;
-        }
-        // with psi = n the self sums equal the cross sums (sA = cB, sB = cA)
-        if (PSI != 0 && (selfA || selfB)) {
-            const R qA = psi_of<R, PSI>(pAt) - psi_of<R, PSI>(mAt);
-            const R qB = psi_of<R, PSI>(pBt) - psi_of<R, PSI>(mBt);
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                if (e3[k] == 0) continue;
-                const double We = (double)(W * (R)e3[k]);
-                sA[k] += We * (double)qA;
-                sB[k] += We * (double)qB;
-            }
-        }
-    }
-    const R gAB = (R)m.g[0][1], gBA = (R)m.g[1][0];
-    const R gAA = (R)m.g[0][0], gBB = (R)m.g[1][1];
-    const R pA = selfA ? psi_of<R, PSI>(nA) : R(0);
-    const R pB = selfB ? psi_of<R, PSI>(nB) : R(0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const R tA = (R)(PSI == 0 ? cB[k] : sA[k]), tB = (R)(PSI == 0 ? cA[k] : sB[k]);
-        FA[k] = sc_force(gAB, nA, (R)cA[k], gAA, pA, tA);
-        FB[k] = sc_force(gBA, nB, (R)cB[k], gBB, pB, tB);
-    }
-}
-
-// The same from a density field laid out [J][z][y][x] (dA, dB).
-template <int D, int ORDER, int PSI, class R>
-__device__ __forceinline__ void site_force(const Member &m,
-                                           const R *__restrict__ dA,
-                                           const R *__restrict__ dB, int x,
-                                           int y, int z, R nA, R nB, R (&FA)[3],
-                                           R (&FB)[3]) {
-    site_force_fn<D, ORDER, PSI, R>(m, x, y, z, nA, nB, FA, FB,
-                                    [&](int t, R &a, R &b) {
-                                        a = dA[t];
-                                        b = dB[t];
-                                    });
-}
-
-// Common velocity, BGK collision with Guo forcing; every f*_i^J is handed to
-// sink(J, i, value, w_i n0_J) as soon as it is formed.
-template <int D, class R, class Sink>
-__device__ __forceinline__ void site_collide(const Member &m,
-                                             const R (&f)[2][Lattice<D>::Q],
-                                             R nA, R nB, const R (&FA)[3],
-                                             const R (&FB)[3], Sink &&sink) {
-    using L = Lattice<D>;
-    double jx[2] = {0, 0}, jy[2] = {0, 0}, jz[2] = {0, 0};  // order-free sums (see site_density)
-#pragma unroll
-    for (int J = 0; J < 2; ++J)
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) {
-            if (L::CX[i]) jx[J] += (double)L::CX[i] * (double)f[J][i];
-            if (L::CY[i]) jy[J] += (double)L::CY[i] * (double)f[J][i];
-            if (D == 3 && L::CZ[i]) jz[J] += (double)L::CZ[i] * (double)f[J][i];
-        }
-    R ux, uy, uz;
-    if (m.omega[0] == m.omega[1]) {
-        // common velocity of Sec. 2
-        const R inv = R(1) / (nA + nB);
-        ux = ((R)(jx[0] + jx[1]) + R(0.5) * (FA[0] + FB[0])) * inv;
-        uy = ((R)(jy[0] + jy[1]) + R(0.5) * (FA[1] + FB[1])) * inv;
-        uz = D == 3 ? ((R)(jz[0] + jz[1]) + R(0.5) * (FA[2] + FB[2])) * inv : R(0);
-    } else {
-        // tau_A != tau_B: each component's momentum and density weighted by
-        // omega_J = 1 / tau_J, the form under which the collisions change the
-        // total momentum by exactly sum_J F_J
-        const R oA = (R)m.omega[0], oB = (R)m.omega[1];
-        const R inv = R(1) / (oA * nA + oB * nB);
-        ux = (oA * ((R)jx[0] + R(0.5) * FA[0]) + oB * ((R)jx[1] + R(0.5) * FB[0])) * inv;
-        uy = (oA * ((R)jy[0] + R(0.5) * FA[1]) + oB * ((R)jy[1] + R(0.5) * FB[1])) * inv;
-        uz = D == 3 ? (oA * ((R)jz[0] + R(0.5) * FA[2]) + oB * ((R)jz[1] + R(0.5) * FB[2])) * inv
-                    : R(0);
-    }
-    const R uu = ux * ux + uy * uy + uz * uz;
-    const R n0[2] = {(R)m.n0[0], (R)m.n0[1]};
-    constexpr Opposite<D> OP = Opposite<D>::make();
-    // Velocities xi and -xi are collided together: with t = omega n_J xi.u,
-    //   E = w [a_J + 9/2 (xi.u) (t + 2 c_f xi.F_J)],  O = w [3 t + 3 c_f xi.F_J],
-    //   a_J = omega n_J (1 - 3/2 u.u) - 3 c_f u.F_J,  c_f = 1 - omega / 2,
-    // f*_xi = (1 - omega) f_xi + (E + O) and f*_-xi = (1 - omega) f_-xi + (E - O)
-    // (eq. lbm with the Guo source).  Every velocity pair then runs the same
-    // operations on sign-flipped operands, which keeps the step exactly
-    // covariant under mirror reflections (see site_density).
-#pragma unroll
-    for (int J = 0; J < 2; ++J) {
-        const R omega = (R)m.omega[J], keep = R(1) - omega, cf = R(1) - R(0.5) * omega;
-        const R *F = J == 0 ? FA : FB;
-        const R nJ = J == 0 ? nA : nB;
-        const R uF = ux * F[0] + uy * F[1] + uz * F[2];
-        const R on = omega * nJ;
-        const R a = on * (R(1) - R(1.5) * uu) - R(3) * cf * uF;
-        double moving = 0, nJx = (double)f[J][0];
-#pragma unroll
-        for (int i = 1; i < L::Q; ++i) {
-            const int ib = OP.opp[i];
-            if (ib < i) continue;
-            R xu = 0, xF = 0;
-            if (L::CX[i]) { xu += (R)L::CX[i] * ux; xF += (R)L::CX[i] * F[0]; }
-            if (L::CY[i]) { xu += (R)L::CY[i] * uy; xF += (R)L::CY[i] * F[1]; }
-            if (D == 3 && L::CZ[i]) { xu += (R)L::CZ[i] * uz; xF += (R)L::CZ[i] * F[2]; }
-            const R w = (R)L::W[i];
-            const R t = on * xu, cF = cf * xF;
-            const R E = w * (a + R(4.5) * xu * (t + R(2) * cF));
-            const R O = w * (R(3) * t + R(3) * cF);
-            const R fp = keep * f[J][i] + (E + O);
-            const R fm = keep * f[J][ib] + (E - O);
-            sink(J, i, fp, w * n0[J]);
-            sink(J, ib, fm, w * n0[J]);
-            moving += (double)fp + (double)fm;
-            nJx += (double)f[J][i] + (double)f[J][ib];
-        }
-        // rest population from the mass balance sum_i f*_i = sum_i f_i (BGK
-        // and the Guo source conserve mass), both sums exact in FP64: rounded
-        // weights and re-rounded sums would otherwise bias the mass by the
-        // same relative amount every step
-        sink(J, 0, (R)(nJx - moving), (R)L::W[0] * n0[J]);
-    }
-}
-
-// Moments that the collision needs at omega = 1: n_J and the total momentum
-// j = sum_J sum_i f_i^J xi_i.  n_J is summed in FP64 (exact for the 2Q
-// storage values) and kept as a pair: mom[J] = its nearest compute-precision
-// value, mom[5 + J] = the remainder.  The collision's rest population uses
-// the exact n_J to close the mass balance, so a steady site conserves mass
-// exactly instead of re-rounding the same sum the same way every step.
-constexpr int NMOM = 7;  // n_A, n_B, j_x, j_y, j_z, rem(n_A), rem(n_B)
-
+//
 // Raw moments of one component's populations, FP64: n = sum_i f_i and
 // j = sum_i xi_i f_i.  In 3D the populations that arrive from one neighbouring
 // column are added first, those from plane z - 1, z and z + 1 in this order
@@ -352,6 +160,226 @@ __device__ __forceinline__ void raw_moments(const R (&f)[Lattice<D>::Q], double 
         }
     }
 }
+
+template <int D, class R>
+__device__ __forceinline__ void site_density(const R (&f)[2][Lattice<D>::Q],
+                                             R &nA, R &nB) {
+    double a = 0, b = 0;  // in the order of the velocities, as the oracle sums
+#pragma unroll
+    for (int i = 0; i < Lattice<D>::Q; ++i) {
+        a += (double)f[0][i];
+        b += (double)f[1][i];
+    }
+    nA = (R)a;
+    nB = (R)b;
+}
+
+// One component of the force: -g n_J c_K - g_JJ psi_J s_J (c, s: stencil sums)
+template <class R> __device__ __forceinline__ R sc_force(R g, R n, R c, R gs, R psi, R s) {
+#pragma clang fp contract(off)
+    const R self = gs * psi * s, gn = -g * n;
+    if constexpr (std::is_same<R, float>::value) return __builtin_fmaf(gn, c, -self);
+    else return __builtin_fma(gn, c, -self);
+}
+
+// Stencil sums of eq. sc_force around site (x, y, z), with the stencil
+// concentrations returned by fetch(t, n_A, n_B) (t = linear site index times
+// UNIT, e.g. a byte offset into an array of (n_A, n_B) pairs), then the force
+// on both components.  The stencil is point-symmetric, so the sum runs over
+// pairs (e, -e): W e (Phi(x + e) - Phi(x - e)).  The difference is exactly
+// odd under e -> -e and the pair sums are accumulated in FP64 (the order-free
+// sums above).  FIELD: fetch(t, n_A, n_B, psi[2]) returns psi as well, from a
+// field that holds it.
+template <int D, int ORDER, int PSI, class R, int UNIT = 1, bool FIELD = false, class Fetch>
+__device__ __forceinline__ void site_force_fn(const Member &m, int x, int y, int z,
+                                              R nA, R nB, R (&FA)[3], R (&FB)[3],
+                                              Fetch &&fetch) {
+    using S = Stencil<D, ORDER>;
+    static_assert(S::point_symmetric(), "stencil table must list e and -e mirrored");
+    double cA[3] = {0, 0, 0}, cB[3] = {0, 0, 0};
+    double sA[3] = {0, 0, 0}, sB[3] = {0, 0, 0};
+    const bool selfA = m.self_on & 1, selfB = m.self_on & 2;
+    // periodic column, row and plane offsets of x + d, y + d, z + d for
+    // d = -2..2, formed once: a stencil neighbour is then two additions
+    int xo[5], yo[5], zo[5];
+#pragma unroll
+    for (int d = -2; d <= 2; ++d) {
+        xo[d + 2] = wrap1(x + d, m.nx) * UNIT;
+        yo[d + 2] = wrap1(y + d, m.ny) * (m.nx * UNIT);
+        zo[d + 2] = D == 3 ? wrap1(z + d, m.nz) * (m.nx * m.ny * UNIT) : 0;
+    }
+#pragma unroll
+    for (int a = S::NE / 2; a < S::NE; ++a) {
+        constexpr auto T = S::T;
+        const int ex = T.e[a][0], ey = T.e[a][1], ez = T.e[a][2];
+        const int tp = zo[2 + ez] + yo[2 + ey] + xo[2 + ex];
+        const int tm = zo[2 - ez] + yo[2 - ey] + xo[2 - ex];
+        R pAt, pBt, mAt, mBt;  // N * UNIT < 2^31 (the callers' forms)
+        R pq[2] = {0, 0}, mq[2] = {0, 0};  // psi of both components
+        if constexpr (FIELD) {
+            fetch(tp, pAt, pBt, pq);
+            fetch(tm, mAt, mBt, mq);
+        } else {
+            fetch(tp, pAt, pBt);
+            fetch(tm, mAt, mBt);
+        }
+        const R dA = pAt - mAt, dB = pBt - mBt;
+        const R W = (R)T.W[a];
+        const int e3[3] = {ex, ey, ez};
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            if (e3[k] == 0) continue;
+            const double We = (double)(W * (R)e3[k]);
+            cA[k] += We * (double)dB;
+            cB[k] += We * (double)dA;
+        }
+        // with psi = n the self sums equal the cross sums (sA = cB, sB = cA)
+        if (PSI != 0 && (selfA || selfB)) {
+            const R qA = FIELD ? pq[0] - mq[0] : psi_of<R, PSI>(pAt) - psi_of<R, PSI>(mAt);
+            const R qB = FIELD ? pq[1] - mq[1] : psi_of<R, PSI>(pBt) - psi_of<R, PSI>(mBt);
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                if (e3[k] == 0) continue;
+                const double We = (double)(W * (R)e3[k]);
+                sA[k] += We * (double)qA;
+                sB[k] += We * (double)qB;
+            }
+        }
+    }
+    const R gAB = (R)m.g[0][1], gBA = (R)m.g[1][0];
+    const R gAA = (R)m.g[0][0], gBB = (R)m.g[1][1];
+    const R pA = selfA ? psi_of<R, PSI>(nA) : R(0);
+    const R pB = selfB ? psi_of<R, PSI>(nB) : R(0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const R tA = (R)(PSI == 0 ? cB[k] : sA[k]), tB = (R)(PSI == 0 ? cA[k] : sB[k]);
+        FA[k] = sc_force(gAB, nA, (R)cA[k], gAA, pA, tA);
+        FB[k] = sc_force(gBA, nB, (R)cB[k], gBB, pB, tB);
+    }
+}
+
+// The same from a density field laid out [J][z][y][x] (dA, dB).
+template <int D, int ORDER, int PSI, class R>
+__device__ __forceinline__ void site_force(const Member &m,
+                                           const R *__restrict__ dA,
+                                           const R *__restrict__ dB, int x,
+                                           int y, int z, R nA, R nB, R (&FA)[3],
+                                           R (&FB)[3]) {
+    site_force_fn<D, ORDER, PSI, R>(m, x, y, z, nA, nB, FA, FB,
+                                    [&](int t, R &a, R &b) {
+                                        a = dA[t];
+                                        b = dB[t];
+                                    });
+}
+
+// The collisions spell their roundings out (fused multiply-adds where they are
+// meant, no contraction elsewhere), so that every kernel that collides a node,
+// and each of its components, forms the same bits.
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) {
+    return __builtin_fma(a, b, c);
+}
+
+// BGK collision with Guo forcing of one component: p is the numerator of the
+// common velocity and inv its denominator's inverse, nx the exact n_J; every
+// f*_i goes to emit(i, value).
+//
+// Velocities xi and -xi are collided together: with t = omega n_J xi.u,
+//   E = w [a_J + 9/2 (xi.u) (t + 2 c_f xi.F_J)],  O = w [3 t + 3 c_f xi.F_J],
+//   a_J = omega n_J (1 - 3/2 u.u) - 3 c_f u.F_J,  c_f = 1 - omega / 2,
+// f*_xi = (1 - omega) f_xi + (E + O) and f*_-xi = (1 - omega) f_-xi + (E - O)
+// (eq. lbm with the Guo source).  Every velocity pair then runs the same
+// operations on sign-flipped operands, which keeps the step exactly
+// covariant under mirror reflections (see site_density).
+template <int D, class R, class Emit>
+__device__ __forceinline__ void collide_component(const R (&f)[Lattice<D>::Q], double nx, R nJ,
+                                                  const R (&F)[3], const R (&p)[3], R inv, R omega,
+                                                  Emit &&emit) {
+#pragma clang fp contract(off)
+    using L = Lattice<D>;
+    constexpr Opposite<D> OP = Opposite<D>::make();
+    const R keep = R(1) - omega, cf = R(1) - R(0.5) * omega, on = omega * nJ;
+    const R u[3] = {p[0] * inv, p[1] * inv, D == 3 ? p[2] * inv : R(0)};
+    R uu = fma_r(u[0], u[0], u[1] * u[1]), uF = fma_r(u[0], F[0], u[1] * F[1]);
+    if (D == 3) {
+        uu = fma_r(u[2], u[2], uu);
+        uF = fma_r(u[2], F[2], uF);
+    }
+    const R a = fma_r(on, fma_r(R(-1.5), uu, R(1)), R(-3) * cf * uF);
+    double moving = 0;
+#pragma unroll
+    for (int i = 1; i < L::Q; ++i) {
+        const int ib = OP.opp[i];
+        if (ib < i) continue;
+        const int c[3] = {L::CX[i], L::CY[i], L::CZ[i]};
+        const int k0 = c[0] ? 0 : c[1] ? 1 : 2;  // the one or two axes of xi
+        const int k1 = k0 == 0 && c[1] ? 1 : k0 < 2 && c[2] ? 2 : k0;
+        R xu = c[k0] > 0 ? u[k0] : -u[k0], xF = c[k0] > 0 ? F[k0] : -F[k0];
+        if (k1 != k0) {
+            xu = fma_r(c[k1] > 0 ? inv : -inv, p[k1], xu);
+            xF = c[k1] > 0 ? xF + F[k1] : xF - F[k1];
+        }
+        const R w = (R)L::W[i], cF = cf * xF, t = on * xu;
+        const R X = fma_r(R(4.5) * xu, fma_r(R(2), cF, t), a);
+        const R O = w * (R(3) * (t + cF));
+        const R fp = fma_r(keep, f[i], fma_r(w, X, O));
+        const R fm = fma_r(keep, f[ib], fma_r(w, X, -O));
+        emit(i, fp);
+        emit(ib, fm);
+        moving += (double)fp + (double)fm;
+    }
+    // rest population from the mass balance sum_i f*_i = sum_i f_i (BGK
+    // and the Guo source conserve mass), both sums exact in FP64: rounded
+    // weights and re-rounded sums would otherwise bias the mass by the
+    // same relative amount every step
+    emit(0, (R)(nx - moving));
+}
+
+// Common velocity and collision of both components; every f*_i^J is handed to
+// sink(J, i, value, w_i n0_J) as soon as it is formed.
+template <int D, class R, class Sink>
+__device__ __forceinline__ void site_collide(const Member &m,
+                                             const R (&f)[2][Lattice<D>::Q],
+                                             R nA, R nB, const R (&FA)[3],
+                                             const R (&FB)[3], Sink &&sink) {
+    using L = Lattice<D>;
+    double nx[2], j[2][3];  // order-free sums (see site_density)
+#pragma unroll
+    for (int J = 0; J < 2; ++J) raw_moments<D, R>(f[J], nx[J], j[J][0], j[J][1], j[J][2]);
+    const R oA = (R)m.omega[0], oB = (R)m.omega[1];
+    R p[3], inv;
+    {
+#pragma clang fp contract(off)
+        if (m.omega[0] == m.omega[1]) {
+            // common velocity of Sec. 2
+            inv = R(1) / (nA + nB);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) p[k] = fma_r(R(0.5), FA[k] + FB[k], (R)(j[0][k] + j[1][k]));
+        } else {
+            // tau_A != tau_B: each component's momentum and density weighted by
+            // omega_J = 1 / tau_J, the form under which the collisions change the
+            // total momentum by exactly sum_J F_J
+            inv = R(1) / (oA * nA + oB * nB);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                p[k] = oA * fma_r(R(0.5), FA[k], (R)j[0][k]) + oB * fma_r(R(0.5), FB[k], (R)j[1][k]);
+        }
+    }
+    const R n0[2] = {(R)m.n0[0], (R)m.n0[1]};
+#pragma unroll
+    for (int J = 0; J < 2; ++J)
+        collide_component<D, R>(f[J], nx[J], J == 0 ? nA : nB, J == 0 ? FA : FB, p, inv,
+                                J == 0 ? oA : oB,
+                                [&](int i, R v) { sink(J, i, v, (R)L::W[i] * n0[J]); });
+}
+
+// Moments that the collision needs at omega = 1: n_J and the total momentum
+// j = sum_J sum_i f_i^J xi_i.  n_J is summed in FP64 (exact for the 2Q
+// storage values) and kept as a pair: mom[J] = its nearest compute-precision
+// value, mom[5 + J] = the remainder.  The collision's rest population uses
+// the exact n_J to close the mass balance, so a steady site conserves mass
+// exactly instead of re-rounding the same sum the same way every step.
+constexpr int NMOM = 7;  // n_A, n_B, j_x, j_y, j_z, rem(n_A), rem(n_B)
 
 template <int D, class R>
 __device__ __forceinline__ void site_moments(const R (&f)[2][Lattice<D>::Q],
@@ -416,15 +444,7 @@ __device__ __forceinline__ void unpack_rem(unsigned w, R (&mm)[NMOM]) {
 // values with the exact n_J: rounded weights (their binary sum is not exactly
 // 1) and re-rounded sums would otherwise bias the mass by the same relative
 // amount every step.
-// The roundings are spelt out (fused multiply-adds where they are meant, no
-// contraction elsewhere), so that every kernel that collides a node, and each
-// of its components, forms the same bits.  p is the momentum (n_A + n_B) u,
-// inv = 1 / (n_A + n_B).
-__device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_r(double a, double b, double c) {
-    return __builtin_fma(a, b, c);
-}
-
+// p is the momentum (n_A + n_B) u, inv = 1 / (n_A + n_B).
 template <int D, class R, class Emit>
 __device__ __forceinline__ void collide_tau1_component(R nJ, R remJ, const R (&F)[3],
                                                        const R (&p)[3], R inv, Emit &&emit) {
@@ -544,8 +564,9 @@ __device__ __forceinline__ void site_collide_store(
         });
         return;
     }
-    site_collide<D, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R ref) {
-        ST::store(base, (long)(J * Lattice<D>::Q + i) * m.N + s, v, ref);
+    site_collide<D, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R) {
+        __builtin_nontemporal_store(ST::encode(v, (R)Lattice<D>::W[i], (R)m.n0[J]),
+                                    base + (long)(J * Lattice<D>::Q + i) * m.N + s);
     });
 }
 
@@ -646,7 +667,7 @@ __device__ __forceinline__ void pull_site_buf(const Member &m, const PopBuf<ST> 
         const int s = zo[1 - L::CZ[i]] + yo[1 - L::CY[i]] + xo[1 - L::CX[i]];
         const int voff = s * (int)sizeof(T), soff = i * b.plane_bytes;
         const R w = (R)L::W[i];
-        R refA = w * n0A, refB = w * n0B;
+        R refA = 0, refB = 0;
         if constexpr (NODE) {
             if (i == 0) {  // the rest populations, FP32 at the node itself
                 const float2 r = m.rest[s];
@@ -666,8 +687,8 @@ __device__ __forceinline__ void pull_site_buf(const Member &m, const PopBuf<ST> 
             f[0][i] = ST::from_node(ra, refA);
             f[1][i] = ST::from_node(rb, refB);
         } else {
-            f[0][i] = ST::from_raw(ra, refA);
-            f[1][i] = ST::from_raw(rb, refB);
+            f[0][i] = ST::decode(ra, w, n0A);
+            f[1][i] = ST::decode(rb, w, n0B);
         }
     }
 }

@@ -104,9 +104,111 @@ __global__ void __launch_bounds__(256)
     site_collide_store<D, ST>(m, f, nA, nB, FA, FB, dst, s);
 }
 
-// ---- tau = 1: moment two-pass
 template <class R> using Pair = typename std::conditional<std::is_same<R, float>::value,
                                                           float2, double2>::type;
+
+// ---- any tau, D3Q19: the density field holds one record per site [z][y][x],
+// (n_A, n_B) or, with psi != n, (n_A, n_B, psi_A, psi_B): psi is then taken
+// once per site instead of once per stencil neighbour.  FP32-compute storage
+// pulls and gathers through buffer descriptors with 32-bit offsets.  Pass 1
+// pulls with ordinary loads and pass 2 the aligned populations
+// non-temporally: measured over all pairs of policies, us per step, 128^3 E6
+// FP32 192 (pass 1 non-temporal too: 188; neither: 200), FP16 101 (121, 118),
+// 160 x 150 x 155 FP32 347 (343, 344), 64^3 FP32 25 (28, 27).  Against the
+// generic kernels below: 128^3 FP32 196 -> 192, FP16 131 -> 101;
+// 100 x 90 x 110 E4 with psi FP32 120 -> 110, FP16 96 -> 78, FP64 202 -> 185.
+// Running pass 2 in z-slabs behind pass 1, so that it pulls from the Infinity
+// Cache, was slower at every slab height (128^3 FP32: 64 planes 192, 32 204,
+// 16 229): cached or not, the populations stream at about 5.5 TB/s.
+template <int PSI> constexpr int kRecord = PSI ? 4 : 2;
+
+template <class ST, int PSI>
+__device__ __forceinline__ void density_site(const Member &m, const typename ST::T *src,
+                                             typename ST::R *dens, int x, int y, int z) {
+    using R = typename ST::R;
+    R f[2][19], nA, nB;
+    if constexpr (std::is_same<R, double>::value)
+        pull_site<3, ST>(m, src, x, y, z, f);
+    else
+        pull_site_buf<ST, PULL_CACHED>(m, make_popbuf<ST, 19>(src, m), x, y, z, f);
+    site_density<3, R>(f, nA, nB);
+    Pair<R> *out = reinterpret_cast<Pair<R> *>(dens + m.dens_off +
+                                               (long)((z * m.ny + y) * m.nx + x) * kRecord<PSI>);
+    out[0] = Pair<R>{nA, nB};
+    if constexpr (PSI != 0) out[1] = Pair<R>{psi_of<R, PSI>(nA), psi_of<R, PSI>(nB)};
+}
+
+template <int ORDER, class ST, int PSI>
+__device__ __forceinline__ void collide_site(const Member &m, const typename ST::T *src,
+                                             typename ST::T *dst, const typename ST::R *dens,
+                                             int x, int y, int z) {
+    using R = typename ST::R;
+    using T = typename ST::T;
+    R f[2][19], nA, nB, FA[3], FB[3];
+    const int s = (z * m.ny + y) * m.nx + x;
+    if constexpr (std::is_same<R, double>::value) {
+        pull_site<3, ST, true>(m, src, x, y, z, f);
+        site_density<3, R>(f, nA, nB);
+        const Pair<R> *rec = reinterpret_cast<const Pair<R> *>(dens + m.dens_off);
+        auto fetch = [&](int t, R &a, R &b, R(&q)[2]) {
+            const Pair<R> n = rec[t];
+            a = n.x;
+            b = n.y;
+            if constexpr (PSI != 0) {
+                const Pair<R> p = rec[t + 1];
+                q[0] = p.x;
+                q[1] = p.y;
+            }
+        };
+        site_force_fn<3, ORDER, PSI, R, kRecord<PSI> / 2, true>(m, x, y, z, nA, nB, FA, FB, fetch);
+        site_collide_store<3, ST>(m, f, nA, nB, FA, FB, dst, s);
+    } else {
+        pull_site_buf<ST, PULL_NT_ALIGNED>(m, make_popbuf<ST, 19>(src, m), x, y, z, f);
+        site_density<3, R>(f, nA, nB);
+        const __amdgpu_buffer_rsrc_t rec = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(dens + m.dens_off), (short)0, m.N * 4 * kRecord<PSI>, BUF_DATA_FORMAT_32);
+        auto fetch = [&](int t, R &a, R &b, R(&q)[2]) {
+            if constexpr (PSI != 0) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rec, t, 0, 0);
+                const unsigned v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+                a = __uint_as_float(v0);
+                b = __uint_as_float(v1);
+                q[0] = __uint_as_float(v2);
+                q[1] = __uint_as_float(v3);
+            } else {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rec, t, 0, 0);
+                const unsigned v0 = v[0], v1 = v[1];  // scalars before the cast
+                a = __uint_as_float(v0);
+                b = __uint_as_float(v1);
+            }
+        };
+        site_force_fn<3, ORDER, PSI, R, 4 * kRecord<PSI>, true>(m, x, y, z, nA, nB, FA, FB, fetch);
+        const PopBuf<ST> db = make_popbuf<ST, 19>(dst, m);
+        const int voff = s * (int)sizeof(T);
+        site_collide<3, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R) {
+            RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), db.r[J], voff,
+                                i * db.plane_bytes);
+        });
+    }
+}
+
+template <class ST, int PSI>
+__global__ void __launch_bounds__(LIN_BLOCK)
+    k_density3(Member m, const typename ST::T *__restrict__ src, typename ST::R *__restrict__ dens) {
+    int x, y, z;
+    if (linear_site<LIN_BLOCK>(m, x, y, z)) density_site<ST, PSI>(m, src, dens, x, y, z);
+}
+
+template <int ORDER, class ST, int PSI>
+__global__ void __launch_bounds__(LIN_BLOCK)
+    k_collide3(Member m, const typename ST::T *__restrict__ src, typename ST::T *__restrict__ dst,
+               const typename ST::R *__restrict__ dens) {
+    int x, y, z;
+    if (linear_site<LIN_BLOCK>(m, x, y, z))
+        collide_site<ORDER, ST, PSI>(m, src, dst, dens, x, y, z);
+}
+
+// ---- tau = 1: moment two-pass
 
 // moment field of a member: (n_A, n_B) pairs [z][y][x], then the planes j_x,
 // j_y (, j_z), then the packed remainders of n_A and n_B (plane 5)
@@ -160,8 +262,9 @@ __device__ __forceinline__ void collide_mom_site(const Member &m,
         });
         return;
     }
-    collide_tau1<D, R>(m, mm, FA, FB, [&](int J, int i, R v, R ref) {
-        ST::store(out, (long)(J * Lattice<D>::Q + i) * m.N + s, v, ref);
+    collide_tau1<D, R>(m, mm, FA, FB, [&](int J, int i, R v, R) {
+        __builtin_nontemporal_store(ST::encode(v, (R)Lattice<D>::W[i], (R)m.n0[J]),
+                                    out + (long)(J * Lattice<D>::Q + i) * m.N + s);
     });
 }
 
@@ -251,8 +354,9 @@ __device__ __forceinline__ void collide_mom_site_buf(const Member &m, const PopB
         });
         return;
     }
-    collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R ref) {
-        RawBuf<T>::store_nt(ST::to_raw(v, ref), db.r[J], voff, i * db.plane_bytes);
+    collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R) {
+        RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), db.r[J], voff,
+                            i * db.plane_bytes);
     });
 }
 
@@ -327,8 +431,9 @@ __global__ void __launch_bounds__(TX *TY)
                                         i * db.plane_bytes);
                 });
             } else {
-                collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R ref) {
-                    RawBuf<T>::store_nt(ST::to_raw(v, ref), db.r[J], voff, i * db.plane_bytes);
+                collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R) {
+                    RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), db.r[J],
+                                        voff, i * db.plane_bytes);
                 });
             }
         }
@@ -566,6 +671,9 @@ template <int D, class ST> constexpr bool buf_form() {
 template <int D, class ST> constexpr bool node_form() {
     return buf_form<D, ST>() && sizeof(typename ST::T) == 2;
 }
+// the record forms of the any-tau two passes: D3Q19, 32-bit offsets, rounding
+// to nearest
+static bool record_form(const StepKey &k) { return k.dim == 3 && !k.big && !k.sr; }
 // stochastic rounding: the 16-bit offset formats
 template <class ST> constexpr bool sr_form() { return sizeof(typename ST::T) == 2; }
 // pass 1 with every load non-temporal: FP32 populations, global reference
@@ -741,6 +849,13 @@ hipError_t launch_two_pass(const StepKey &k, const Member &m, const void *src,
                                    (const T *)src, (R *)dens);
                 hipLaunchKernelGGL((k_collide_mom<D, O, ST, P>), g, b, 0, st, m,
                                    (const T *)src, (T *)dst, (const R *)dens);
+            } else if (D == 3 && record_form(k)) {
+                if constexpr (D == 3) {
+                    hipLaunchKernelGGL((k_density3<ST, P>), g, b, 0, st, m, (const T *)src,
+                                       (R *)dens);
+                    hipLaunchKernelGGL((k_collide3<O, ST, P>), g, b, 0, st, m, (const T *)src,
+                                       (T *)dst, (const R *)dens);
+                }
             } else {
                 hipLaunchKernelGGL((k_density<D, ST>), g, b, 0, st, m,
                                    (const T *)src, (R *)dens);
@@ -765,6 +880,11 @@ bool node_two_pass(const StepKey &k, NodeLaunch *dn, NodeLaunch *sn,
             dn->func = k.mom ? (void *)&k_moments<D, ST> : (void *)&k_density<D, ST>;
             sn->func = k.mom ? (void *)&k_collide_mom<D, O, ST, P>
                              : (void *)&k_collide<D, O, ST, P>;
+            if constexpr (D == 3)
+                if (!k.mom && record_form(k)) {
+                    dn->func = (void *)&k_density3<ST, P>;
+                    sn->func = (void *)&k_collide3<O, ST, P>;
+                }
             dn->grid = sn->grid = dim3(linear_blocks(m, m.znum, LIN_BLOCK));
             dn->block = sn->block = dim3(LIN_BLOCK, 1, 1);
             dn->shmem = sn->shmem = 0;
