@@ -120,18 +120,33 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
     const R gx = (R)(J ? m.g[1][0] : m.g[0][1]), gs = (R)(J ? m.g[1][1] : m.g[0][0]);
     const bool self = (m.self_on >> J) & 1, any_self = m.self_on & 3;
     const R n0 = (R)m.n0[J];
+    // psi beside the collision, before the exchange's barrier, and the self sums
+    // without a branch per stencil pair, over zeros where there are no self
+    // couplings: us per step with psi, E4 FP32, 128^3 76.6 -> 73.5, 63^3 19.6 ->
+    // 18.8, 30^3 8.7 -> 8.2.  E6 FP32 and E4 FP64, short of registers, were
+    // slower that way (100 x 90 x 110: 57.9 -> 59.2, 57.0 -> 59.6).
+    constexpr bool EARLY = PSI != 0 && ORDER == 4 && !F64;
 
     auto load_ring = [&](int z, R(&v)[2]) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) v[c] = RawVal<R>::load(ipr, pv[c], z * nxy * 2 * SZ);
     };
-    auto put_ring = [&](int slot, const R(&v)[2]) {
+    auto take_psi = [&](const R(&v)[2], R(&q)[2]) {
+        q[0] = q[1] = R(0);
+        if (any_self) {
+            q[0] = psi_of<R, PSI>(v[0]);
+            q[1] = psi_of<R, PSI>(v[1]);
+        }
+    };
+    auto put_ring = [&](int slot, const R(&v)[2], const R(&q)[2]) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             if (!pon[c]) continue;
             ring[slot][pl[c]] = v[c];
             // psi of the own component, at the index the other lane's n has
-            if constexpr (PSI != 0)
+            if constexpr (EARLY)
+                pring[slot][pl[c] ^ 1] = q[c];
+            else if constexpr (PSI != 0)
                 if (any_self) pring[slot][pl[c] ^ 1] = psi_of<R, PSI>(v[c]);
         }
     };
@@ -147,9 +162,10 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
     auto wrapz = [&](int z) { return ((z % m.nz) + m.nz) % m.nz; };
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
-        R v[2];
+        R v[2], q[2] = {0, 0};
         load_ring(wrapz(z0 - 1 - RR + s), v);
-        put_ring(s, v);
+        if constexpr (EARLY) take_psi(v, q);
+        put_ring(s, v, q);
     }
     R jn[3];
     unsigned remn = 0;
@@ -175,7 +191,7 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
         constexpr int KIND = decltype(kind)::value;
         const R j[3] = {jn[0], jn[1], jn[2]};
         const unsigned remw = remn;
-        R pre[2];  // the next round's loads, waited for after the collision
+        R pre[2], preq[2] = {0, 0};  // the next round's loads, waited for after the collision
         if constexpr (KIND < 2) {
             load_ring(wrap1(z0 + RR + k, m.nz), pre);
             load_mom(wrap1(z0 + k, m.nz), jn, remn);
@@ -202,7 +218,7 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
                 for (int q = 0; q < 3; ++q)
                     if (e3[q]) c[q] += (double)(W * (R)e3[q]) * (double)d;
                 if constexpr (PSI != 0)
-                    if (any_self) {
+                    if (EARLY || any_self) {
                         const R p = pat(vx, vy, RR + vz) - pat(-vx, -vy, RR - vz);
 #pragma unroll
                         for (int q = 0; q < 3; ++q)
@@ -270,6 +286,7 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
                 }
             }
         }
+        if constexpr (KIND < 2 && EARLY) take_psi(pre, preq);
 #pragma unroll
         for (int st = 0; st < G::STAGES; ++st) {
             if (st > 0) {
@@ -280,7 +297,7 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
             }
             __syncthreads();
             if constexpr (KIND < 2)
-                if (st == 0) put_ring(slot[0], pre);
+                if (st == 0) put_ring(slot[0], pre, preq);
             if constexpr (KIND == 0) continue;
 #pragma unroll
             for (int q = 0; q < NX; ++q) {
