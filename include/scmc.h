@@ -91,8 +91,8 @@ typedef enum {
 } scmc_storage;
 typedef enum {
     SCMC_KERNEL_AUTO = 0,        /* tau_A = tau_B = 1: TWO_PASS_MOM; otherwise
-                                    FUSED where it exists (D3Q19, E4/E6,
-                                    FP32/FP16/BF16), else TWO_PASS;
+                                    TWO_PASS (FUSED when tile is set and the
+                                    design exists for the problem);
                                     scmc_autotune may choose another */
     SCMC_KERNEL_TWO_PASS = 1,    /* density pass + stream/force/collide pass */
     SCMC_KERNEL_FUSED = 2,       /* one z-marching kernel per step (D3Q19 with
@@ -218,7 +218,11 @@ int scmc_destroy(scmc_sim *s);
 int scmc_set_density(scmc_sim *s, const double *nA, const double *nB);
 
 /* Advance nsteps >= 0 time steps, asynchronously.  With graph steps k > 0
- * (scmc_set_graph_steps) runs of k steps replay one instantiated hipGraph. */
+ * (scmc_set_graph_steps) runs of k steps replay one instantiated hipGraph.
+ * At tau = 1 the moment two-pass takes the steps of a call in blocks (a
+ * graph's length, else up to 64): pass 1 once, the steps between from moments
+ * to moments, pass 2 once; longer calls are faster per step.  The result does
+ * not depend on how the steps are divided into calls. */
 int scmc_step(scmc_sim *s, int64_t nsteps);
 int scmc_set_graph_steps(scmc_sim *s, int k);
 int scmc_synchronize(scmc_sim *s);
@@ -330,14 +334,16 @@ int scmc_flat_equilibrium(const scmc_problem *p, int lx, const double *guess,
                           int64_t *steps);
 
 /* Many independent lattices advanced together over one tile list (the
- * paper's sweep over droplet sizes and couplings, Sec. 4).  The moment
- * two-pass runs the members in chunks of whole members (a member with 48 MB
- * or more of moments alone, the others packed up to 48 MB), pass 1 and then
- * pass 2 of each chunk: a chunk of one member launches as a single lattice
- * does, the others one workgroup per 256-site tile.  The fused designs run
- * one persistent launch per step.  Members may differ in size and
- * couplings; they must share lattice, stencil, tau and storage.  Member calls
- * take the member index i. */
+ * paper's sweep over droplet sizes and couplings, Sec. 4).  The passes of the
+ * moment two-pass run over chunks of whole members (a member with 48 MB or
+ * more of moments alone, the others packed up to 48 MB): a chunk of one member
+ * launches as a single lattice does, the others one workgroup per 256-site
+ * tile.  In a call of several steps the steps between the first pass 1 and
+ * the last pass 2 run from moments to moments, one launch per step for a group
+ * of consecutive members (up to 64, and up to 112 MB of moments unless one
+ * member alone has more).  The fused designs run one persistent launch per
+ * step.  Members may differ in size and couplings; they must share lattice,
+ * stencil, tau and storage.  Member calls take the member index i. */
 typedef struct scmc_batch scmc_batch;
 int scmc_batch_workspace_bytes(const scmc_problem *ps, int count, size_t *out);
 int scmc_batch_create(const scmc_problem *ps, int count, void *d_ws,
@@ -346,7 +352,7 @@ int scmc_batch_destroy(scmc_batch *b);  /* waits for the stream, as scmc_destroy
 int scmc_batch_set_density(scmc_batch *b, int i, const double *nA,
                            const double *nB);
 /* Advances every member nsteps steps.  Members are independent lattices:
- * with the moment two-pass a call runs chunk by chunk, each chunk a block of
+ * with the moment two-pass a call runs group by group, each group a block of
  * steps (a graph's length, else up to 64) before the next, so members pass
  * through different steps while the call's work runs on the stream; all
  * are at the batch's step count once it has completed. */
