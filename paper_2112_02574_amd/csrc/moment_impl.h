@@ -28,8 +28,8 @@
 // so a call of k steps equals k calls of one step bit for bit.
 //
 // us per step against pass 1 and pass 2 of every step: E6 128^3 FP32 122 ->
-// 64, 150 x 141 x 165 FP32 337 -> 120, 192^3 FP16 343 -> 244, 100 x 84 x 92
-// FP64 102 -> 37, E4 with psi 63^3 FP32 27.4 -> 18.1.  At 128^3 a lane issues
+// 64, 150 x 141 x 165 FP32 337 -> 120, 192^3 FP16 343 -> 236, 100 x 84 x 92
+// FP64 102 -> 37, E4 with psi 63^3 FP32 27.4 -> 17.8.  At 128^3 a lane issues
 // 325 vector instructions per plane (430 with 16 exchanged populations
 // instead of 12 sums), which keeps the SIMDs busy 86 % of the time.
 #pragma once
@@ -166,16 +166,22 @@ __device__ __forceinline__ void mom_column(const Member &m, const typename ST::R
 
     // round k collides plane z = z0 - 1 + k; the ring's slot s holds plane z - RR + s
     auto wrapz = [&](int z) { return ((z % m.nz) + m.nz) % m.nz; };
+    // all loads before the first wait: the stores to the ring are under a branch
+    // that the compiler moves no load across.  us per step with a wait per
+    // plane -> one wait: 25 x 26 x 23 BF16 8.3 -> 7.8, 63^3 FP32 with psi 18.1
+    // -> 17.8, 192^3 FP16 244 -> 236, 128^3 FP32 64.6 -> 64.1 (124 x 142 x 148
+    // with psi 96 -> 97)
+    R v0[NSLOT][2], jn[3];
+    unsigned remn = 0;
+#pragma unroll
+    for (int s = 0; s < NSLOT; ++s) load_ring(wrapz(z0 - 1 - RR + s), v0[s]);
+    load_mom(wrapz(z0 - 1), jn, remn);
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
-        R v[2], q[2] = {0, 0};
-        load_ring(wrapz(z0 - 1 - RR + s), v);
-        if constexpr (EARLY) take_psi(v, q);
-        put_ring(s, v, q);
+        R q[2] = {0, 0};
+        if constexpr (EARLY) take_psi(v0[s], q);
+        put_ring(s, v0[s], q);
     }
-    R jn[3];
-    unsigned remn = 0;
-    load_mom(wrapz(z0 - 1), jn, remn);
     __syncthreads();
 
     // the other component's value at the low corner of the node's stencil box
