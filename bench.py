@@ -14,14 +14,15 @@ multiple of 2^11 (Sec. 4), inside the timed region when that falls there, and
 once after it for the reported observables otherwise.
 
 Prints one JSON line: MLUPS (million lattice-site updates per second, both
-components), the roofline of the step kernel (algorithmic bytes 4 Q s per
-site = 304 B for FP32 over the event-timed kernel time, against the 8 TB/s
-HBM peak), the HBM traffic measured by rocprofv3 counters for the same
-kernel source when available, and the FP64 CPU oracle timed on a bounded
-sample of the same workload.  Beside it go the step rates of the other
+components), the roofline of the step kernels (the bytes a step moves over the
+event-timed kernel time, against the 8 TB/s HBM peak; the moment design moves
+24 B of moments per site each way in FP32 and the populations, 304 B, once per
+block of steps, and is bound by its vector instructions instead), the HBM
+traffic measured by rocprofv3 counters for the same kernel source when
+available, and the FP64 CPU oracle timed on a bounded sample of the same
+workload.  Beside it go the step rates of the other
 storage formats (FP64, FP16 and BF16 offsets) on the same droplet and of the
-48-member batched sweep (the moment two-pass over member chunks, in 64-step
-graphs), each over a short timed run.
+48-member batched sweep (in 64-step graphs), each over a short timed run.
 """
 import argparse
 import csv
@@ -79,7 +80,10 @@ def profile_commands(tag):
 
 
 PROFILE_COMMANDS = profile_commands("f32")
-KERNEL_SOURCES = ["paper_2112_02574_amd/csrc/step_kernels.hip",
+KERNEL_SOURCES = ["paper_2112_02574_amd/csrc/moment_impl.h",
+                  "paper_2112_02574_amd/csrc/moment_inst.hip",
+                  "paper_2112_02574_amd/csrc/moment_kernels.hip",
+                  "paper_2112_02574_amd/csrc/step_kernels.hip",
                   "paper_2112_02574_amd/csrc/fused_impl.h",
                   "paper_2112_02574_amd/csrc/fused_inst.hip",
                   "paper_2112_02574_amd/csrc/fused_kernels.hip",
@@ -98,7 +102,7 @@ def kernel_source_hash():
 
 
 def measured_traffic(n_sites):
-    """HBM bytes per step launch from the committed rocprofv3 counter summary,
+    """HBM bytes per step from the committed rocprofv3 counter summary,
     or None when it is missing or was taken on a different kernel source."""
     try:
         with open(TRAFFIC_JSON) as fh:
@@ -107,22 +111,23 @@ def measured_traffic(n_sites):
         return None
     if t.get("kernel_source_hash") != kernel_source_hash() or t.get("sites") != n_sites:
         return None
-    return t.get("hbm_bytes_per_launch")
+    return t.get("hbm_bytes_per_step")
 
 
 def _finite(v):
     return v if isinstance(v, (int, float)) and v == v and abs(v) != float("inf") else None
 
 
-STEP_KERNEL = re.compile(r"scmc::kb?_(fused|density|collide|moments|collide_mom)(_buf|_lds)?<")
+STEP_KERNEL = re.compile(r"scmc::kb?_(fused|density3?|collide3?|moments|collide_mom|mom_step)"
+                         r"(_buf|_lds)?<")
 
 
 def summarize_profiles(outdir, tag="f32", L=128):
     """Write the profiles/ summaries from the rocprofv3 CSV output of the
-    commands of profile_commands(tag) (run from the repository root).  A step
-    is one launch of each step kernel (one for the fused designs, two for the
-    two-pass ones, two per member chunk for the batch); durations and
-    counters are summed over them."""
+    commands of profile_commands(tag) (run from the repository root).  The
+    durations and counters of all step kernels are summed over the program's
+    steps (20 + 300 in the trace run, 5 + 20 in the counter runs): a call of
+    several steps runs pass 1 and pass 2 once per block of up to 64 steps."""
     import csv
     from paper_2112_02574_amd import inputs
     sub = "" if tag == "f32" else "_" + tag
@@ -153,21 +158,16 @@ def summarize_profiles(outdir, tag="f32", L=128):
     step_rows = [r for r in stats if STEP_KERNEL.search(r["Name"])
                  and "density64" not in r["Name"] and "kb_" not in r["Name"]]
     names = [r["Name"].split("(")[0] for r in step_rows]
-    step_us = sum(float(r["AverageNs"]) for r in step_rows) / 1e3
-    per_step = 1
+    step_us = sum(float(r["TotalDurationNs"]) for r in step_rows) / 320 / 1e3
     if tag == "batch48":
-        # the batch's two-pass launches (its process also runs the FP64 flat
-        # stages and the autotuner's candidates): one pass 1 and one pass 2
-        # per member chunk and step (tile-list kernels kb_*, or for a chunk
-        # of one member the single-lattice ones), several steps chunk by
-        # chunk.  The trace run's last 300 steps are the launches from the
+        # the process also runs the FP64 flat stages and the autotuner's
+        # candidates: the trace run's last 300 steps are the launches from the
         # end back to where the pass-1 launches have covered every member's
-        # sites (in 256-site blocks) 300 times; the step time is their
-        # summed duration over 300
+        # sites (in 256-site blocks) once per block of up to 64 steps
         seq = [r for r in rows(f"prof{sub}_trace", "_kernel_trace.csv")
-               if re.search(r"scmc::kb?_(moments|collide_mom)_buf<", r["Kernel_Name"])]
+               if re.search(r"scmc::kb?_(moments_buf|collide_mom_buf|mom_step)<", r["Kernel_Name"])]
         seq.sort(key=lambda r: int(r["Start_Timestamp"]))
-        need = 300 * sum(-(-m["L"] ** 3 // 256) * 256 for m in inputs.batch_members())
+        need = -(-300 // 64) * sum(-(-m["L"] ** 3 // 256) * 256 for m in inputs.batch_members())
         got, i = 0, len(seq)
         while got < need and i > 0:
             i -= 1
@@ -177,7 +177,6 @@ def summarize_profiles(outdir, tag="f32", L=128):
         if got != need:
             raise SystemExit(f"batch trace: pass-1 launches cover {got} sites, not {need}")
         window = seq[i:]
-        per_step = round(len(window) / 300)
         names = sorted({r["Kernel_Name"].split("(")[0] for r in window})
         step_us = sum(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
                       for r in window) / 300 / 1e3
@@ -189,10 +188,9 @@ def summarize_profiles(outdir, tag="f32", L=128):
     for nm in (names if have_counters else []):
         f, a = mean_counter(f"prof{sub}_fetch", nm)
         w, b = mean_counter(f"prof{sub}_write", nm)
-        # a batch step launches each kernel once per member chunk (the counter
-        # runs of the batch take 20 warm-up and 20 timed steps)
-        per = max(1, round(a / 40)) if tag == "batch48" else 1
-        fetch, write, nf, nw = fetch + f * per, write + w * per, nf + a, nw + b
+        # the counter runs take 5 + 20 steps (the batch's 1 + 20 + 20)
+        n = 41 if tag == "batch48" else 25
+        fetch, write, nf, nw = fetch + f * a / n, write + w * b / n, nf + a, nw + b
     cf, _ = mean_counter("prof_copy_fetch", "__amd_rocclr_copyBuffer")
     cw, _ = mean_counter("prof_copy_write", "__amd_rocclr_copyBuffer")
     copy_bytes = 1024 * (1 << 20)
@@ -207,10 +205,8 @@ def summarize_profiles(outdir, tag="f32", L=128):
                 r["Name"].split("(")[0], r["Calls"], float(r["AverageNs"]) / 1e3,
                 float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3, float(r["Percentage"])))
         lines += ["", "Step kernels: %s." % ", ".join("`%s`" % n for n in names), "",
-                  "One step (the %d launches of a step, summed, averaged over the trace run's last "
-                  "300 steps): %.1f us = %.0f MLUPS; algorithmic %d B/site -> %.0f GB/s (%.1f%% of "
-                  "8 TB/s)." % (per_step, step_us, N / step_us, bps, bps * N / step_us / 1e3,
-                                bps * N / step_us / 1e3 / 80),
+                  "One step (all step launches of the trace run's timed steps, divided by them): "
+                  "%.1f us = %.0f MLUPS." % (step_us, N / step_us),
                   "", "No HBM traffic counters: rocprofv3 --pmc runs of this program ended with a "
                   "segmentation fault of the profiled process before the first step.", ""]
         with open(trace_md, "w") as fh:
@@ -223,8 +219,8 @@ def summarize_profiles(outdir, tag="f32", L=128):
                "copy_calibration": {"bytes": copy_bytes, "fetch_size_kib": round(cf, 1),
                                     "write_size_kib": round(cw, 1), "fetch_scale": round(sf, 4),
                                     "write_scale": round(sw, 4)},
-               "hbm_bytes_per_launch": round(hbm), "algorithmic_bytes_per_launch": bps * N,
-               "ratio_to_algorithmic": round(hbm / (bps * N), 4),
+               "hbm_bytes_per_step": round(hbm), "population_bytes_per_step": bps * N,
+               "ratio_to_populations": round(hbm / (bps * N), 4),
                "kernel_source_hash": kernel_source_hash(),
                "commands": [cmds[k] for k in ("fetch", "write", "copy_fetch", "copy_write")]}
     with open(traffic_json, "w") as fh:
@@ -238,19 +234,12 @@ def summarize_profiles(outdir, tag="f32", L=128):
             r["Name"].split("(")[0], r["Calls"], float(r["AverageNs"]) / 1e3,
             float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3, float(r["Percentage"])))
     lines += ["", "Step kernels: %s." % ", ".join("`%s`" % n for n in names),
-              "", "One step: %.1f us = %.0f MLUPS; algorithmic %d B/site -> %.0f GB/s "
-              "(%.1f%% of 8 TB/s)." % (step_us, N / step_us, bps, bps * N / step_us / 1e3,
-                                       bps * N / step_us / 1e3 / 80),
+              "", "One step (all step launches over the run's 320 steps): %.1f us = %.0f MLUPS."
+              % (step_us, N / step_us),
               "", "HBM traffic per step (rocprofv3 counters summed over the step kernels, scaled by a "
               "1 GiB copy): FETCH_SIZE %.0f KiB x %.3f + WRITE_SIZE %.0f KiB x %.3f = %.1f MB, "
-              "%.3f x the algorithmic %.1f MB." % (
+              "%.3f x the %.1f MB of one read and one write of the populations." % (
                   fetch, sf, write, sw, hbm / 1e6, hbm / (bps * N), bps * N / 1e6), ""]
-    if tag == "batch48":
-        lines[-1:-1] = ["A batch step launches pass 1 and pass 2 once per member chunk (%d launches: a "
-                        "chunk of one member as a single lattice, the others one workgroup per 256-site "
-                        "tile); the step time is the launches' summed duration "
-                        "over the trace run's last 300 steps, divided by 300, and the trace's averages "
-                        "above are per chunk." % per_step, ""]
     with open(trace_md, "w") as fh:
         fh.write("\n".join(lines))
     print(open(trace_md).read())
@@ -294,14 +283,16 @@ def summarize_designs(outdir, L=128):
         for r in rows(sub, "_counter_collection.csv"):
             k = r["Kernel_Name"].split("(")[0]
             acc.setdefault(k, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
-        return {k: {c: sum(v) / len(v) for c, v in d.items()} for k, d in acc.items()}
+        # per step of the counter runs' 25, per launch of the copy
+        per = 25 if sub.startswith("dprof") else None
+        return {k: {c: sum(v) / (per or len(v)) for c, v in d.items()} for k, d in acc.items()}
 
     cf = mean_by_kernel("prof_copy_fetch")["__amd_rocclr_copyBuffer"]["FETCH_SIZE"]
     cw = mean_by_kernel("prof_copy_write")["__amd_rocclr_copyBuffer"]["WRITE_SIZE"]
     sf, sw = (1 << 30) / (cf * 1024), (1 << 30) / (cw * 1024)
     lines = ["# FP32 step designs on the 128^3 droplet: time, traffic, instruction mix", "",
-             "D3Q19 E6 droplet 128^3, FP32 populations, tau = 1. Per step kernel: the mean duration "
-             "of the trace run, its LDS per workgroup, HBM traffic from FETCH_SIZE / WRITE_SIZE "
+             "D3Q19 E6 droplet 128^3, FP32 populations, tau = 1. Per step kernel: the duration per "
+             "step of the trace run, its LDS per workgroup, HBM traffic from FETCH_SIZE / WRITE_SIZE "
              "scaled by a 1 GiB copy (FETCH x%.3f, WRITE x%.3f), and the instructions the SQ counters "
              "count per 64 sites (one wavefront's worth; the designs give a wavefront different "
              "numbers of sites)." % (sf, sw), "",
@@ -324,7 +315,7 @@ def summarize_designs(outdir, L=128):
                 continue
             t = next(r for r in trace if r["Kernel_Name"].split("(")[0] == k)
             lds = int(t["LDS_Block_Size"])
-            us = float(st["AverageNs"]) / 1e3
+            us = float(st["TotalDurationNs"]) / 320 / 1e3  # per step of the run's 320
             h = (fetch.get(k, {}).get("FETCH_SIZE", 0) * sf + write.get(k, {}).get("WRITE_SIZE", 0) * sw) * 1024
             q = sq.get(k, {})
             per = N / 64.0
@@ -412,11 +403,27 @@ def _timed(step, steps, stream):
     return ev0.elapsed_time(ev1) / steps
 
 
-# bytes per site update (read + write every population once) by storage;
+# bytes of one read and one write of every population of a site by storage;
 # node storage keeps the rest populations in FP32: 36 x 2 + 2 x 4 each way
 STORAGE_BYTES = {"f64": 608, "f32": 304, "f16_offset": 152, "bf16_offset": 152,
                  "f16_node": 160, "bf16_node": 160}
+# bytes per site and step from moment field to moment field (D3Q19): n_A, n_B,
+# j and the remainders, read and written; node storage also its rest
+# populations
+MOMENT_BYTES = {"f64": 96, "f16_node": 64, "bf16_node": 64}
+STEP_BLOCK = 64  # steps between one pass 1 and the next pass 2 in a long call
 PRECISION_JSON = os.path.join(ROOT, "profiles", "precision_256cube_asym.json")
+
+
+def moved_bytes(name, kernel, steps, graph=0):
+    """Bytes per site that one step of a call of ``steps`` steps moves, averaged
+    over a block: the moment design reads the populations and writes moments
+    once, steps from moments to moments, and writes the populations once."""
+    pops = STORAGE_BYTES[name]
+    if KERNEL_NAMES[kernel] != "two_pass_mom":
+        return pops
+    k, mom = min(graph or STEP_BLOCK, steps), MOMENT_BYTES.get(name, 48)
+    return (pops + mom + (k - 1) * mom) / k
 
 
 def _storage_kinds(scmc):
@@ -425,7 +432,7 @@ def _storage_kinds(scmc):
             ("bf16_node", scmc.BF16_NODE))
 
 
-def _storage_rate(args, scmc, shape, g, storage, n0, init, dev, stream, bps):
+def _storage_rate(args, scmc, shape, g, storage, n0, init, dev, stream, name):
     s = scmc.Sim(scmc.problem(scmc.D3Q19, scmc.E6, shape, g=g, storage=storage, n0=n0),
                  device=dev, stream=stream)
     if storage != scmc.F64:
@@ -435,6 +442,7 @@ def _storage_rate(args, scmc, shape, g, storage, n0, init, dev, stream, bps):
     kernel, tile = s.scmc_config()
     s.close()
     N = shape[0] * shape[1] * shape[2]
+    bps = round(moved_bytes(name, kernel, args.variant_steps), 1)
     return {"MLUPS": round(N / (ms * 1e3), 1), "kernel": KERNEL_NAMES[kernel], "tile": list(tile),
             "bytes_per_site": bps, "hbm_frac": round(bps * N / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
 
@@ -453,10 +461,8 @@ def variants(args, L, R0, bulk, init, dev, stream):
     for name, storage in _storage_kinds(scmc):
         if name == "f32":
             continue
-        out[name] = _storage_rate(args, scmc, (L, L, L), G_SYM, storage, n0, init, dev, stream,
-                                  STORAGE_BYTES[name])
-    # the 256^3 asymmetric droplet: its moment field outgrows the caches, so
-    # the moment two-pass runs in z-slabs
+        out[name] = _storage_rate(args, scmc, (L, L, L), G_SYM, storage, n0, init, dev, stream, name)
+    # the 256^3 asymmetric droplet: its moment field outgrows the caches
     bulk_asym, _ = scmc.scmc_flat_equilibrium(
         scmc.problem(scmc.D3Q19, scmc.E6, (128, 128, 128), g=G_ASYM, storage=scmc.F64),
         lx=128, guess=inputs.FLAT_GUESS[-0.2], tol=1e-10, device=dev, stream=stream)
@@ -470,8 +476,7 @@ def variants(args, L, R0, bulk, init, dev, stream):
     c5 = {"workload": f"D3Q19 E6 {Lb}^3 B-rich droplet R0={Lb / 4:g} g_AB=1.8 g_AA=-0.2 psi=n",
           "accuracy_steps": acc.get("steps")}
     for name, storage in _storage_kinds(scmc):
-        r = _storage_rate(args, scmc, (Lb, Lb, Lb), G_ASYM, storage, n0_b, init_b, dev, stream,
-                          STORAGE_BYTES[name])
+        r = _storage_rate(args, scmc, (Lb, Lb, Lb), G_ASYM, storage, n0_b, init_b, dev, stream, name)
         a = acc.get("runs", {}).get(name, {})
         r["abs_err_R_s_vs_f64"] = a.get("abs_err_R_s")
         r["rel_err_sigma_s_vs_f64"] = a.get("rel_err_sigma_s")
@@ -502,14 +507,12 @@ def _batch_rate(args, bulk, bulk_asym, dev, stream, steps, graph=64):
                                                     bulk=bulks[m["g"][0][0]]))
     b.scmc_batch_set_graph_steps(graph)
     # untimed: the first run of `graph` steps captures and instantiates the
-    # graph (72 launches per step), a one-time cost outside the step rate
+    # graph, a one-time cost outside the step rate
     b.scmc_batch_step(max(graph, 1))
     ms = _timed(b.scmc_batch_step, steps, stream)
     sites = sum(m["L"] ** 3 for m in members)
-    gbs = 4 * 19 * 4 * sites / (ms * 1e-3) / 1e9
     r = {"MLUPS": round(sites / (ms * 1e3), 1), "sites": sites, "members": len(members),
-         "tile": list(tile), "grid": b.scmc_batch_config()[1], "graph_steps": graph,
-         "hbm_frac": round(gbs / HBM_PEAK_GBS, 4)}
+         "tile": list(tile), "grid": b.scmc_batch_config()[1], "graph_steps": graph}
     b.close()
     return r
 
@@ -602,13 +605,12 @@ def run(args):
     ms_per_step = wall * 1e3 / args.steps
     mlups = N * args.steps / wall / 1e6
     kernel_ms = step_ms / args.steps
-    bps = STORAGE_BYTES[args.storage]
-    bytes_alg = bps * N  # read + write of every population once (FP32: 2 x 19 x 4 B each way)
-    achieved = bytes_alg / (kernel_ms * 1e-3) / 1e9
+    bps = moved_bytes(args.storage, kernel, min(args.steps, OBS_EVERY), args.graph)
+    achieved = bps * N / (kernel_ms * 1e-3) / 1e9
     traffic = measured_traffic(N) if args.storage == "f32" else None
     # the streaming half of the step without arithmetic, in the same buffers:
-    # the bandwidth ceiling of any design that moves each population once
-    # (it overwrites the state, so it runs after the observables)
+    # the bandwidth ceiling of any design that moves each population once per
+    # step (it overwrites the state, so it runs after the observables)
     copy_bytes = 4 * 19 * {"f64": 8, "f32": 4}.get(args.storage, 2) * N
     copy_gbs = copy_bytes / (sim.scmc_pull_copy(200) * 1e-6) / 1e9
     line = {
@@ -633,13 +635,15 @@ def run(args):
                    # the per-site sums (n_J, momentum, force, the mass closure)
                    # accumulate FP32 values in FP64, order-free
                    "site_sums": "f64"},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "vector_instructions" if KERNEL_NAMES[kernel] == "two_pass_mom"
+                     and args.steps > 1 else "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "kernel_ms": round(kernel_ms, 5),
-                     "bytes_per_site": bps,
+                     "bytes_per_site": round(bps, 1),
                      "pull_copy_GBs": round(copy_gbs, 1),
                      "pull_copy_frac": round(copy_gbs / HBM_PEAK_GBS, 4),
-                     "achieved_over_pull_copy": round(achieved / copy_gbs, 4)},
+                     # one copy of the populations over one step
+                     "pull_copy_over_step_time": round(copy_bytes / copy_gbs / 1e6 / kernel_ms, 4)},
         "observables": {"dP": _finite(obs["dP"]), "R_s": _finite(obs["R_s"]),
                         "sigma_s": _finite(obs["sigma_s"]), "step": obs["step"],
                         "mass": stats["mass"].tolist(), "max_u": _finite(stats["max_u"]),
