@@ -233,12 +233,16 @@ int scmc_synchronize(scmc_sim *s);
  * caller's device populations src to dst (distinct buffers of 2*Q*N values of
  * the storage type, in the device layout described at scmc_set_density), on
  * the current device and the given stream (NULL = default).  The kernel
- * design is chosen as scmc_create does; the density / moment field of the
- * two-pass designs lives in a static device array of the library,
- * SCMC_STATIC_SCRATCH_BYTES on every GPU it runs on, held until the process
- * ends.  Nothing is allocated.  Every call on one GPU shares that array and
- * fully rewrites the part it reads, so calls that overlap on one GPU (other
- * streams, other threads) race and must be serialised by the caller.
+ * design is chosen as scmc_create does, except that AUTO at tau != 1 takes
+ * FUSED where it exists; the density / moment field of the two-pass designs
+ * lives in a static device array of the library, SCMC_STATIC_SCRATCH_BYTES on
+ * every GPU it runs on, held until the process ends.  Nothing is allocated.
+ * Every two-pass call on one GPU shares that array and fully rewrites the
+ * part it reads, so calls that overlap on one GPU (other streams, other
+ * threads) race and must be serialised by the caller.  FUSED uses no field:
+ * at tau != 1 overlapping AUTO calls on D3Q19 with FP32 / FP16 / BF16 storage
+ * are independent (a caller that serialises its calls can ask for TWO_PASS,
+ * the faster design on small lattices).
  * Returns SCMC_ENOSPACE when the lattice needs more than the array (7 values
  * of the compute precision per site: 2.39M sites FP32/FP16/BF16, 1.19M FP64),
  * SCMC_EUNSUPPORTED for stochastic rounding (its step counter lives in a

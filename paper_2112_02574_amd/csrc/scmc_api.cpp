@@ -402,18 +402,21 @@ Member member_of(const scmc_problem &p) {
     return m;
 }
 
-// resolve the kernel design and the fused tile
+// resolve the kernel design and the fused tile; own_field: the moment /
+// density field belongs to the handle, and no other call writes it
 int choose_kernel(const scmc_problem &p, const StepKey &k, int *kernel,
-                  int *tile) {
+                  int *tile, bool own_field = true) {
     int t[3] = {p.tile[0], p.tile[1], p.tile[2]};
     // the default is the moment two-pass design at tau = 1 and the any-tau two
     // passes otherwise, the fastest untuned choices: us per step at tau = 0.8,
     // E6, against the fused design's default tile (64, 8, 16), 64^3 FP32 25
     // against 120, 128^3 FP32 192 against 203, FP16 101 against 133,
     // 160 x 150 x 155 FP32 345 against 591.  The autotuner may pick a fused one
-    // (128^3 FP32 with (128, 4, 16): 181).
+    // (128^3 FP32 with (128, 4, 16): 181).  The allocation-free step's field is
+    // one array per GPU: there AUTO takes the fused design at tau != 1, which
+    // needs no field, so that calls on several streams share no memory.
     if (k.node || p.kernel == SCMC_KERNEL_TWO_PASS || p.kernel == SCMC_KERNEL_TWO_PASS_MOM ||
-        (p.kernel == SCMC_KERNEL_AUTO && t[0] == 0) ||
+        (p.kernel == SCMC_KERNEL_AUTO && t[0] == 0 && (own_field || k.mom)) ||
         (p.kernel == SCMC_KERNEL_AUTO && p.rounding == SCMC_ROUND_STOCHASTIC)) {
         *kernel = SCMC_KERNEL_TWO_PASS;
         const bool lds = k.mom == 2;
@@ -1395,7 +1398,7 @@ int scmc_step_static(const scmc_problem *p, const void *src, void *dst, void *st
                            "node storage keeps its reference field in a workspace: use scmc_step");
     const StepKey key = key_of(*p);
     int kernel = 0, tile[3] = {0, 0, 0};
-    rc = choose_kernel(*p, key, &kernel, tile);
+    rc = choose_kernel(*p, key, &kernel, tile, false);
     if (rc) return static_fail(rc, "no kernel design for this problem");
     const Member m = member_of(*p);
     // the field that scmc_workspace_bytes plans for the same problem: 7
