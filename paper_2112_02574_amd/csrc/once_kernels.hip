@@ -109,20 +109,27 @@ __global__ void __launch_bounds__(ONCE_THREADS)
 
 // Boxes of 8 x 4 x 4 nodes at E4 (360 with the halo) and 4 x 4 x 4 at E6 (512):
 // of the boxes that a workgroup's lanes hold, none was faster.  One launch pays
-// as long as the boxes fit the chip at once, about two workgroups per CU, and
-// one in FP64, whose pulls are twice as wide.  us per call from Python, whose
-// own 9.4 us hide what is below, two launches against one: FP32 E4 24^3 12.2,
-// 9.5; 40^3 (500 boxes) 12.0, 10.7; 48^3 (864) 11.9, 16.6; E6 32^3 (512) 12.2,
-// 10.5; 40^3 (1 000) 12.1, 19.2; FP64 E4 32^3 (256) 12.1, 9.6; 40^3 (500) 12.1,
-// 14.8; E6 24^3 (216) 12.1, 9.6; 32^3 (512) 12.1, 15.9.
+// while the boxes fit the chip at one workgroup per CU: a workgroup is one
+// round of loads and the pulls of its halo, and a second one on a CU doubles
+// both.  us per call in a loop of calls, two launches against one, psi = n: FP32
+// E4 24^3 (108 boxes) 8.1, 6.6; 32^3 (256) 8.5, 7.3; 33^3 (405) 9.0, 10.8; 40^3
+// (500) 10.4, 11.9; E6 24^3 (216) 9.0, 7.8; 25^3 (343) 9.5, 11.5; 32^3 (512) 9.2,
+// 12.5; FP16 E6 24^3 8.9, 7.1; 32^3 9.1, 10.8.  With psi the two passes take it
+// of every stencil neighbour, and two workgroups per CU still pay: FP32 E4 40^3
+// 13.5, 12.7; E6 24^3 14.3, 8.8; 32^3 13.9, 13.5; in FP64, whose pulls are twice
+// as wide, one: E4 32^3 14.5, 11.0.  Two sides that take two launches although
+// their boxes fit: E6 with psi = n in FP64 (8^3 8.4, 9.2; 24^3 11.2, 11.4;
+// 16 x 32 x 32 10.7, 11.4) and what one workgroup of the two passes holds, 256
+// nodes, at E6 (5^3 5.9, 7.1).
 bool step_once_shape(const StepKey &k, const Member &m, MomShape *g) {
     if (k.dim != 3 || k.mom != 1 || k.node || k.sr || (k.order != 4 && k.order != 6)) return false;
+    if (k.order == 6 && !k.psi && (k.storage == ST_F64 || m.N <= 256)) return false;
     *g = MomShape{std::min(k.order == 4 ? 8 : 4, m.nx), std::min(4, m.ny), std::min(4, m.nz)};
     g->ntx = (m.nx + g->w - 1) / g->w;
     g->nty = (m.ny + g->h - 1) / g->h;
     g->nchunks = (m.nz + g->zc - 1) / g->zc;
     const long boxes = (long)g->ntx * g->nty * g->nchunks;
-    return boxes <= (k.storage == ST_F64 ? 256 : 512);
+    return boxes <= (k.psi && k.storage != ST_F64 ? 512 : 256);
 }
 
 hipError_t launch_step_once(const StepKey &k, const Member &m, const MomShape &g, const void *src,
