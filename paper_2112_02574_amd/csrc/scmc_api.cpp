@@ -19,6 +19,7 @@
 #include "../../include/scmc.h"
 #include "lattice.h"
 #include "scmc_internal.h"
+#include "step_rules.h"
 
 using namespace scmc;
 
@@ -884,9 +885,17 @@ int direct_step_sim(scmc_sim *s) {
     return SCMC_OK;
 }
 
-// Whether a block of steps of this handle runs on the moment field alone.
-bool mom_steps_on(const scmc_sim *s) {
-    return s->mom_ok && s->c.kernel == SCMC_KERNEL_TWO_PASS && s->c.key.mom && !s->c.key.sr;
+StorageWidth storage_width(const StepKey &k) {
+    return k.storage == ST_F64 ? WIDE_64 : k.storage == ST_F32 ? WIDE_32 : WIDE_16;
+}
+
+// Whether a block of k steps of this handle runs on the moment field alone.
+bool mom_steps_on(const scmc_sim *s, int64_t k) {
+    const StepKey &key = s->c.key;
+    if (k < 2 || !s->mom_ok || s->c.kernel != SCMC_KERNEL_TWO_PASS || !key.mom || key.sr)
+        return false;
+    return s->lat.dim == 3 ||
+           mom2_steps_pay(storage_width(key), key.order, key.psi, s->lat.m.N, k);
 }
 
 // The launches of k >= 2 steps from buffer par that stay in the moment field:
@@ -941,7 +950,7 @@ int mom_steps(scmc_sim *s, int64_t k, int par, Emit &&emit) {
 // k steps of a single lattice outside graphs.
 int direct_steps_sim(scmc_sim *s, int64_t k) {
     Common &c = s->c;
-    if (k < 2 || !mom_steps_on(s)) {
+    if (!mom_steps_on(s, k)) {
         int rc = SCMC_OK;
         for (int64_t t = 0; t < k && !rc; ++t) rc = direct_step_sim(s);
         return rc;
@@ -1079,7 +1088,7 @@ int build_graph(Common &c, int k, int par, bool batch, const Member &m,
     };
     int cur = par, rc = SCMC_OK;
     if (two_pass) rc = batch_steps(two_pass, k, par, add);
-    const bool mom = sim && k >= 2 && mom_steps_on(sim);
+    const bool mom = sim && mom_steps_on(sim, k);
     if (mom) rc = mom_steps(sim, k, par, add);
     for (int t = 0; !two_pass && !mom && t < k && !rc; ++t) {
         for (size_t ch = 0; ch + 1 < chunks.size() && !rc; ++ch) {

@@ -4,7 +4,9 @@ The rules that choose between launches of equal results weigh their times, and
 each case here was timed on both sides.  The workspace tells the routes apart.
 Its first part is the two population buffers, its next the moment field.  A
 single step in one launch leaves the moment field alone, which the two passes
-write.
+write.  A block of an even number of steps that runs both passes of every step
+leaves the populations of the step before in the second buffer, one on the
+moment field uses that buffer as its second field.
 """
 import numpy as np
 import pytest
@@ -54,3 +56,34 @@ def test_one_launch_while_the_boxes_fit_the_chip(shape, stencil, storage, psi, o
     s.scmc_synchronize()
     assert bool((field == 0xA5).all()) == one
     s.close()
+
+
+def _on_the_moment_field(s, p, steps, graph=0):
+    """Whether a call of `steps` (even) ran on the moment field."""
+    if graph:
+        s.scmc_set_graph_steps(graph)
+    s.scmc_step(steps)
+    s.scmc_synchronize()
+    n, off = scmc.state_bytes(p), _buffer_bytes(p)
+    left = s.ws[off:off + n].clone()
+    s.close()
+    t = _sim(p)
+    for _ in range(steps - 1):
+        t.scmc_step(1)
+    t.scmc_synchronize()
+    same = torch.equal(t.ws[off:off + n], left)
+    t.close()
+    return not same
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("shape,stencil,storage,psi,steps,moments", [
+    ((64, 64), 4, scmc.F32, False, 2, True), ((300, 400), 4, scmc.F16_OFF, False, 2, True),
+    ((300, 401), 4, scmc.F16_OFF, False, 2, False), ((300, 401), 4, scmc.F16_OFF, False, 4, True),
+    ((512, 512), 6, scmc.BF16_OFF, False, 8, False), ((600, 600), 4, scmc.F16_OFF, True, 4, True),
+    ((640, 640), 8, scmc.F16_OFF, True, 4, False), ((512, 512), 4, scmc.F32, False, 2, False),
+    ((512, 512), 4, scmc.F32, False, 4, True), ((1024, 1024), 8, scmc.F32, True, 4, False),
+    ((1024, 1024), 8, scmc.F32, False, 4, True), ((1024, 1024), 8, scmc.F64, True, 2, True)])
+def test_planes_take_moment_steps_where_they_pay(shape, stencil, storage, psi, steps, moments, graph):
+    p = _problem(shape, stencil, storage, psi)
+    assert _on_the_moment_field(_sim(p), p, steps, steps * graph) == moments
