@@ -30,7 +30,8 @@ SCMC_MOM_COMBOS(SCMC_EXTERN)
 // The search below runs over columns for a given number of planes per chunk
 // (mom_columns) and over that number; the members of a batched launch share
 // the chunk length, and their workgroups the rounds.
-static constexpr double kPlaneUs = 27, kFillPlanes = 3.5;  // in units of a wavefront's 0.06 us
+static constexpr double kWaveUs = 0.06;
+static constexpr double kPlaneUs = 27, kFillPlanes = 3.5;  // in units of kWaveUs, in planes
 
 // The fewest wavefront-planes per plane of the member: columns, largest first.
 static MomShape mom_columns(const Member &m, int order, int rows) {
@@ -55,7 +56,7 @@ static MomShape mom_columns(const Member &m, int order, int rows) {
     return best;
 }
 
-static MomShape mom_shape(const Member &m, int order, int rows, int ncu) {
+static MomShape mom_shape(const Member &m, int order, int rows, int ncu, double *us) {
     const int r = order == 4 ? 1 : 2;
     MomShape best{};
     double best_cost = 1e300;
@@ -81,6 +82,7 @@ static MomShape mom_shape(const Member &m, int order, int rows, int ncu) {
             }
         }
     }
+    *us = kWaveUs * best_cost;
     return best;
 }
 
@@ -116,10 +118,11 @@ static int mom_threads(const StepKey &k, const MomShape &g) {
     return (std::max(2 * (g.w + 2) * (g.h + 2), (g.w + r2) * (g.h + r2)) + 63) / 64 * 64;
 }
 
-bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape) {
+bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape,
+                   double *us) {
     const MomKernel f = mom_kernel(k);
     if (!f.func) return false;
-    *shape = mom_shape(m, k.order, f.rows, compute_units());
+    *shape = mom_shape(m, k.order, f.rows, compute_units(), us);
     if (shape->w < 1) return false;
     node->func = f.func;
     node->grid = dim3(shape->ntx * shape->nty * shape->nchunks);

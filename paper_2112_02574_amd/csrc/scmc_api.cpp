@@ -211,6 +211,7 @@ struct scmc_sim {
     bool mom_ok = false;  // blocks of steps can stay in the moment field
     NodeLaunch mom_node{};
     MomShape mom_shape{};
+    double mom_us = 0;  // D3Q19: a step's time by the launch model
     int mom2 = 0;  // D2Q9: the most steps that a launch of mom_node makes
     bool have_prev = false;  // convergence monitor: a previous check exists
     double prev_dP = 0;
@@ -889,13 +890,19 @@ StorageWidth storage_width(const StepKey &k) {
     return k.storage == ST_F64 ? WIDE_64 : k.storage == ST_F32 ? WIDE_32 : WIDE_16;
 }
 
+// sites in rows that are not a multiple of 16 (mom_steps_pay)
+int64_t ragged_sites(const Member &m) { return m.nx % 16 ? m.N : 0; }
+
 // Whether a block of k steps of this handle runs on the moment field alone.
 bool mom_steps_on(const scmc_sim *s, int64_t k) {
     const StepKey &key = s->c.key;
     if (k < 2 || !s->mom_ok || s->c.kernel != SCMC_KERNEL_TWO_PASS || !key.mom || key.sr)
         return false;
-    return s->lat.dim == 3 ||
-           mom2_steps_pay(storage_width(key), key.order, key.psi, s->lat.m.N, k);
+    const Member &m = s->lat.m;
+    return s->lat.dim == 3
+               ? mom_steps_pay(storage_width(key), key.node, key.order, key.psi, m.N,
+                               ragged_sites(m), s->mom_us, k)
+               : mom2_steps_pay(storage_width(key), key.order, key.psi, m.N, k);
 }
 
 // The launches of k >= 2 steps from buffer par that stay in the moment field:
@@ -1274,7 +1281,7 @@ int scmc_create(const scmc_problem *p, void *d_ws, size_t ws_bytes,
     bind(c, pl, c.ws, stats_blocks(s->lat.m));
     s->lat.m.step_ctr = c.ctr;
     s->mom_ok = s->lat.dim == 3
-                    ? node_mom_step(c.key, s->lat.m, &s->mom_node, &s->mom_shape)
+                    ? node_mom_step(c.key, s->lat.m, &s->mom_node, &s->mom_shape, &s->mom_us)
                     : node_mom2_steps(c.key, s->lat.m, &s->mom_node, &s->mom_shape, &s->mom2);
     *out = s;
     return SCMC_OK;

@@ -139,8 +139,10 @@ struct MomShape {
 };
 // The kernel of one such step of m and its launch shape; false: none for this
 // key.  Kernel arguments: Member, MomShape, const void *in, void *out (moment
-// fields), int in_slot, int out_slot (slots of their (n_A, n_B) pairs).
-bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape);
+// fields), int in_slot, int out_slot (slots of their (n_A, n_B) pairs).  us: what
+// the launch model gives for a step.
+bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape *shape,
+                   double *us);
 int compute_units();  // of the current device (256 where it cannot be asked)
 // D2Q9 (moment2d_kernels.hip): up to *steps steps per launch.  Kernel
 // arguments: Member, MomShape, int steps, const void *in, void *out.
