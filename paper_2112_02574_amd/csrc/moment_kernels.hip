@@ -132,16 +132,17 @@ bool node_mom_step(const StepKey &k, const Member &m, NodeLaunch *node, MomShape
 }
 
 bool node_batch_mom_step(const StepKey &k, const std::vector<Member> &ms, int first_member,
-                         NodeLaunch *node, MomList *list) {
+                         NodeLaunch *node, MomList *list, double *us) {
     const MomKernel f = mom_kernel(k);
     if (!f.batch || ms.empty() || ms.size() > (size_t)MOM_LIST) return false;
     const int ncu = compute_units();
     std::vector<MomShape> g;
-    int nzmax = 1;
+    int nzmax = 1, waves = 1;
     for (const Member &m : ms) {
         g.push_back(mom_columns(m, k.order, f.rows));
         if (g.back().w < 1) return false;
         nzmax = std::max(nzmax, m.nz);
+        waves = std::max(waves, (2 * (g.back().w + 2) * (g.back().h + 2) + 63) / 64);
     }
     double best_cost = 1e300;
     int best = 1;
@@ -155,6 +156,7 @@ bool node_batch_mom_step(const StepKey &k, const std::vector<Member> &ms, int fi
             best = len;
         }
     }
+    *us = kWaveUs * best_cost * (kPlaneUs + waves);
     list->n = (int)ms.size();
     int first = 0, threads = 64;
     for (size_t i = 0; i < ms.size(); ++i) {

@@ -231,11 +231,14 @@ struct BatchOp {
 
 // Ops [op0, op1) of consecutive members (from `member` on), which advance a
 // block of steps before the next group starts.  mom: the steps between the
-// first pass 1 and the last pass 2 stay in the moment field.
+// first pass 1 and the last pass 2 can stay in the moment field; they do where
+// that pays (mom_steps_pay).
 struct BatchGroup {
     size_t op0 = 0, op1 = 0;
     int member = 0;
     bool mom = false;
+    int64_t sites = 0, ragged = 0;
+    double us = 0;
     NodeLaunch node{};
     MomList list{};
 };
@@ -1014,7 +1017,9 @@ template <class Emit> int batch_steps(scmc_batch *b, int64_t k, int par, Emit &&
     Common &c = b->c;
     int rc = SCMC_OK;
     for (BatchGroup &g : b->groups) {
-        if (k >= 2 && g.mom) {
+        if (k >= 2 && g.mom &&
+            mom_steps_pay(storage_width(c.key), false, c.key.order, c.key.psi, g.sites, g.ragged,
+                          g.us, k)) {
             const int last = par ^ (int)((k - 1) & 1);
             const Member &m0 = b->lats[g.member].m;
             const scmc_problem &p0 = b->lats[g.member].p;
@@ -1841,7 +1846,11 @@ static void batch_set_ops(scmc_batch *b) {
             for (int i : members_of[q]) ms.push_back(b->lats[i].m);
         }
         g.op1 = 2 * q;
-        g.mom = node_batch_mom_step(c.key, ms, g.member, &g.node, &g.list);
+        for (const Member &m : ms) {
+            g.sites += m.N;
+            g.ragged += ragged_sites(m);
+        }
+        g.mom = node_batch_mom_step(c.key, ms, g.member, &g.node, &g.list, &g.us);
         b->groups.push_back(g);
     }
 }

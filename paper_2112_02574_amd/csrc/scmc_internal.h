@@ -160,9 +160,10 @@ struct MomList {
     } e[MOM_LIST];
 };
 // Kernel arguments: const Member *, MomList, const void *in, void *out (the
-// moment fields' base, to which each member's dens_off is added).
+// moment fields' base, to which each member's dens_off is added).  us as in
+// node_mom_step.
 bool node_batch_mom_step(const StepKey &k, const std::vector<Member> &ms, int first_member,
-                         NodeLaunch *node, MomList *list);
+                         NodeLaunch *node, MomList *list, double *us);
 
 // ---- one step of a small lattice in one launch (once_kernels.hip): whether m
 // takes it, and the boxes; launch_two_pass asks for it by itself

@@ -114,3 +114,26 @@ NODE = scmc.F16_NODE
 def test_boxes_take_moment_steps_where_they_pay(shape, stencil, storage, psi, steps, moments):
     p = _problem(shape, stencil, storage, psi)
     assert _on_the_moment_field(_sim(p), p, steps) == moments
+
+
+@pytest.mark.parametrize("L,count,stencil,storage,steps,moments", [
+    (32, 8, 6, scmc.F16_OFF, 8, False), (36, 4, 4, scmc.BF16_OFF, 8, False),
+    (24, 16, 6, scmc.F16_OFF, 8, True), (40, 8, 4, scmc.F16_OFF, 8, True),
+    (32, 4, 6, scmc.F32, 2, False), (32, 4, 6, scmc.F32, 4, True), (32, 4, 6, scmc.F64, 2, True)])
+def test_batches_take_moment_steps_where_they_pay(L, count, stencil, storage, steps, moments):
+    p = _problem((L, L, L), stencil, storage)
+    n, size = scmc.state_bytes(p), _buffer_bytes(p)
+    state = inputs.droplet(L, L, L, R=L / 4)
+
+    def second(calls):
+        b = scmc.Batch([p] * count)
+        for i in range(count):
+            b.scmc_batch_set_density(i, *state)
+        for k in calls:
+            b.scmc_batch_step(k)
+        torch.cuda.synchronize()
+        out = b.ws[count * size:2 * count * size].view(count, size)[:, :n].clone()
+        b.close()
+        return out
+
+    assert torch.equal(second([steps]), second([1] * (steps - 1))) != moments
