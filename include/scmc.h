@@ -221,8 +221,10 @@ int scmc_set_density(scmc_sim *s, const double *nA, const double *nB);
  * (scmc_set_graph_steps) runs of k steps replay one instantiated hipGraph.
  * At tau = 1 the moment two-pass takes the steps of a call in blocks (a
  * graph's length, else up to 64): pass 1 once, the steps between from moments
- * to moments, pass 2 once; longer calls are faster per step.  The result does
- * not depend on how the steps are divided into calls. */
+ * to moments, pass 2 once; longer calls are faster per step.  Where that is no
+ * faster (16-bit storage of some sizes, calls of a few steps) it runs both
+ * passes of every step.  The result does not depend on how the steps are
+ * divided into calls. */
 int scmc_step(scmc_sim *s, int64_t nsteps);
 int scmc_set_graph_steps(scmc_sim *s, int k);
 int scmc_synchronize(scmc_sim *s);
@@ -342,11 +344,11 @@ int scmc_flat_equilibrium(const scmc_problem *p, int lx, const double *guess,
  * moment two-pass run over chunks of whole members (a member with 48 MB or
  * more of moments alone, the others packed up to 48 MB): a chunk of one member
  * launches as a single lattice does, the others one workgroup per 256-site
- * tile.  In a call of several steps the steps between the first pass 1 and
- * the last pass 2 run from moments to moments, one launch per step for a group
- * of consecutive members (up to 64, and up to 112 MB of moments unless one
- * member alone has more).  The fused designs run one persistent launch per
- * step.  Members may differ in size and couplings; they must share lattice,
+ * tile.  In a call of several steps, where that is the faster way, the steps
+ * between the first pass 1 and the last pass 2 run from moments to moments,
+ * one launch of up to 64 members (more take further launches) per step for a
+ * group of consecutive members of up to 112 MB of moments, or of one member
+ * that alone has more.  The fused designs run one persistent launch per step.  Members may differ in size and couplings; they must share lattice,
  * stencil, tau and storage.  Member calls take the member index i. */
 typedef struct scmc_batch scmc_batch;
 int scmc_batch_workspace_bytes(const scmc_problem *ps, int count, size_t *out);

@@ -239,8 +239,11 @@ struct BatchGroup {
     bool mom = false;
     int64_t sites = 0, ragged = 0;
     double us = 0;
-    NodeLaunch node{};
-    MomList list{};
+    struct Launch {  // of up to MOM_LIST members; a moment step makes them all
+        NodeLaunch node{};
+        MomList list{};
+    };
+    std::vector<Launch> launches;
 };
 
 struct scmc_batch {
@@ -904,7 +907,7 @@ bool mom_steps_on(const scmc_sim *s, int64_t k) {
     const Member &m = s->lat.m;
     return s->lat.dim == 3
                ? mom_steps_pay(storage_width(key), key.node, key.order, key.psi, m.N,
-                               ragged_sites(m), s->mom_us, k)
+                               ragged_sites(m), s->mom_us, 1, k)
                : mom2_steps_pay(storage_width(key), key.order, key.psi, m.N, k);
 }
 
@@ -1019,7 +1022,7 @@ template <class Emit> int batch_steps(scmc_batch *b, int64_t k, int par, Emit &&
     for (BatchGroup &g : b->groups) {
         if (k >= 2 && g.mom &&
             mom_steps_pay(storage_width(c.key), false, c.key.order, c.key.psi, g.sites, g.ragged,
-                          g.us, k)) {
+                          g.us, (int)g.launches.size(), k)) {
             const int last = par ^ (int)((k - 1) & 1);
             const Member &m0 = b->lats[g.member].m;
             const scmc_problem &p0 = b->lats[g.member].p;
@@ -1029,11 +1032,12 @@ template <class Emit> int batch_steps(scmc_batch *b, int64_t k, int par, Emit &&
             for (size_t j = g.op0; j < g.op1 && !rc; j += 2)
                 rc = emit_op(b, b->ops[j], c.pop[par], c.pop[1 - par], field[at], emit);
             const Member *dm = b->d_members;
-            for (int64_t t = 1; t < k && !rc; ++t, at ^= 1) {
-                std::vector<void *> a = {(void *)&dm, (void *)&g.list, (void *)&field[at],
-                                         (void *)&field[1 - at]};
-                rc = emit(g.node, a);
-            }
+            for (int64_t t = 1; t < k && !rc; ++t, at ^= 1)
+                for (size_t l = 0; l < g.launches.size() && !rc; ++l) {
+                    std::vector<void *> a = {(void *)&dm, (void *)&g.launches[l].list,
+                                             (void *)&field[at], (void *)&field[1 - at]};
+                    rc = emit(g.launches[l].node, a);
+                }
             for (size_t j = g.op0 + 1; j < g.op1 && !rc; j += 2)
                 rc = emit_op(b, b->ops[j], c.pop[last], c.pop[1 - last], field[0], emit);
             continue;
@@ -1850,7 +1854,18 @@ static void batch_set_ops(scmc_batch *b) {
             g.sites += m.N;
             g.ragged += ragged_sites(m);
         }
-        g.mom = node_batch_mom_step(c.key, ms, g.member, &g.node, &g.list, &g.us);
+        // a chunk of more than MOM_LIST members: full launches first (129 of 24^3:
+        // 64, 64 and 1 fill 256 CUs in one round each, 43 three times in two)
+        g.mom = true;
+        for (size_t m0 = 0; m0 < ms.size() && g.mom; m0 += MOM_LIST) {
+            const size_t m1 = std::min(ms.size(), m0 + MOM_LIST);
+            BatchGroup::Launch launch;
+            double us = 0;
+            g.mom = node_batch_mom_step(c.key, {ms.begin() + m0, ms.begin() + m1},
+                                        g.member + (int)m0, &launch.node, &launch.list, &us);
+            g.us += us;
+            g.launches.push_back(launch);
+        }
         b->groups.push_back(g);
     }
 }

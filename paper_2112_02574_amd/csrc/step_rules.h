@@ -59,11 +59,21 @@ inline bool mom2_steps_pay(StorageWidth w, int order, bool psi, int64_t sites, i
 // steps gain (32^3 8.8, 6.8).  Short calls, FP16 48^3 E6: two steps 11.8, 13.1;
 // four 11.8, 12.4; 56^3 E4 two 13.3, 14.8, sixteen 13.2, 13.1; 60^3 E6 four 18.3,
 // 16.9; with psi 64^3 two 21.0, 21.9, four 20.4, 20.4.
+// A group of more members than a launch takes makes several launches per step,
+// each of which fills the chip by itself: all types then weigh the model against
+// the two passes, FP64 and FP32 with a tenth to spare (E6 FP32, us per step: 65
+// members of 24^3 60, 42; 129 of them 112, 75; 100 of 25^3 137, 69; 70 of 30^3 150,
+// 83; FP64 70 of 16^3 39, 29, with psi, at twice the model's time, 59, 70; FP16
+// with psi 129 of 24^3 148, 117; 130 of 16^3 54, 70).
 inline bool mom_steps_pay(StorageWidth w, bool node, int order, bool psi, int64_t sites,
-                          int64_t ragged, double us, int64_t steps) {
+                          int64_t ragged, double us, int launches, int64_t steps) {
+    if (w != WIDE_16 && launches > 1 &&
+        us * (w == WIDE_64 && order == 6 && psi ? 2 : 1) >
+            0.9 * (7 + (w == WIDE_64 ? 11.5e-5 : 6e-5) * (double)sites))
+        return false;
     if (w == WIDE_64) return !(order == 6 && psi && sites < 120000);
     if (w == WIDE_32) return steps >= 3 || sites < 80000 || sites > 135000;
-    if (sites < 80000 || (psi && sites >= 300000)) return true;
+    if (launches == 1 && (sites < 80000 || (psi && sites >= 300000))) return true;
     if (sites < 300000 && steps < (psi || node || sites > 200000 ? 4 : 8)) return false;
     const double n = (double)sites;
     const double passes = std::max(5.5 + 3.5e-5 * n, 9.3 + 2.2e-5 * n) *

@@ -116,24 +116,32 @@ def test_boxes_take_moment_steps_where_they_pay(shape, stencil, storage, psi, st
     assert _on_the_moment_field(_sim(p), p, steps) == moments
 
 
+def _batch(L, count, p, calls):
+    """The batch's state after the calls: (second buffer, fields)."""
+    n, size = scmc.state_bytes(p), _buffer_bytes(p)
+    b = scmc.Batch([p] * count)
+    for i in range(count):
+        b.scmc_batch_set_density(i, *inputs.droplet(L, L, L, R=L / 4 * (1 - 0.2 * i / count)))
+    for k in calls:
+        b.scmc_batch_step(k)
+    torch.cuda.synchronize()
+    second = b.ws[count * size:2 * count * size].view(count, size)[:, :n].clone()
+    fields = np.stack([b.scmc_batch_get_fields(i) for i in range(count)])
+    b.close()
+    return second, fields
+
+
 @pytest.mark.parametrize("L,count,stencil,storage,steps,moments", [
     (32, 8, 6, scmc.F16_OFF, 8, False), (36, 4, 4, scmc.BF16_OFF, 8, False),
     (24, 16, 6, scmc.F16_OFF, 8, True), (40, 8, 4, scmc.F16_OFF, 8, True),
-    (32, 4, 6, scmc.F32, 2, False), (32, 4, 6, scmc.F32, 4, True), (32, 4, 6, scmc.F64, 2, True)])
+    (32, 4, 6, scmc.F32, 2, False), (32, 4, 6, scmc.F32, 4, True), (32, 4, 6, scmc.F64, 2, True),
+    # a launch's members, then two and three launches per step
+    (24, 64, 6, scmc.F32, 4, True), (24, 65, 6, scmc.F32, 4, True), (24, 129, 6, scmc.F32, 4, True),
+    (24, 70, 4, scmc.F64, 4, True), (25, 70, 4, scmc.BF16_OFF, 8, False), (16, 70, 6, scmc.F32, 4, False)])
 def test_batches_take_moment_steps_where_they_pay(L, count, stencil, storage, steps, moments):
     p = _problem((L, L, L), stencil, storage)
-    n, size = scmc.state_bytes(p), _buffer_bytes(p)
-    state = inputs.droplet(L, L, L, R=L / 4)
-
-    def second(calls):
-        b = scmc.Batch([p] * count)
-        for i in range(count):
-            b.scmc_batch_set_density(i, *state)
-        for k in calls:
-            b.scmc_batch_step(k)
-        torch.cuda.synchronize()
-        out = b.ws[count * size:2 * count * size].view(count, size)[:, :n].clone()
-        b.close()
-        return out
-
-    assert torch.equal(second([steps]), second([1] * (steps - 1))) != moments
+    block, fields = _batch(L, count, p, [steps])
+    before, _ = _batch(L, count, p, [1] * (steps - 1))
+    assert torch.equal(block, before) != moments
+    _, singles = _batch(L, count, p, [1] * steps)
+    np.testing.assert_array_equal(fields, singles)
