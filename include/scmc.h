@@ -341,15 +341,17 @@ int scmc_flat_equilibrium(const scmc_problem *p, int lx, const double *guess,
 
 /* Many independent lattices advanced together over one tile list (the
  * paper's sweep over droplet sizes and couplings, Sec. 4).  The passes of the
- * moment two-pass run over chunks of whole members (a member with 48 MB or
+ * two-pass designs run over chunks of whole members (a member with 48 MB or
  * more of moments alone, the others packed up to 48 MB): a chunk of one member
- * launches as a single lattice does, the others one workgroup per 256-site
- * tile.  In a call of several steps, where that is the faster way, the steps
- * between the first pass 1 and the last pass 2 run from moments to moments,
- * one launch of up to 64 members (more take further launches) per step for a
- * group of consecutive members of up to 112 MB of moments, or of one member
- * that alone has more.  The fused designs run one persistent launch per step.  Members may differ in size and couplings; they must share lattice,
- * stencil, tau and storage.  Member calls take the member index i. */
+ * launches as a single lattice does at tau = 1, the others one workgroup per
+ * 256-site tile.  In a call of several steps at tau = 1, where that is the
+ * faster way, the steps between the first pass 1 and the last pass 2 run from
+ * moments to moments, one launch of up to 64 members (more take further
+ * launches) per step for a group of consecutive members of up to 112 MB of
+ * moments, or of one member that alone has more.  The fused designs run one
+ * persistent launch per step.  Members may differ in size and couplings; they
+ * must share lattice, stencil, tau and storage.  Member calls take the member
+ * index i. */
 typedef struct scmc_batch scmc_batch;
 int scmc_batch_workspace_bytes(const scmc_problem *ps, int count, size_t *out);
 int scmc_batch_create(const scmc_problem *ps, int count, void *d_ws,
@@ -358,7 +360,7 @@ int scmc_batch_destroy(scmc_batch *b);  /* waits for the stream, as scmc_destroy
 int scmc_batch_set_density(scmc_batch *b, int i, const double *nA,
                            const double *nB);
 /* Advances every member nsteps steps.  Members are independent lattices:
- * with the moment two-pass a call runs group by group, each group a block of
+ * with the two-pass designs a call runs group by group, each group a block of
  * steps (a graph's length, else up to 64) before the next, so members pass
  * through different steps while the call's work runs on the stream; all
  * are at the batch's step count once it has completed. */

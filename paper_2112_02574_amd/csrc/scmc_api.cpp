@@ -420,9 +420,14 @@ int choose_kernel(const scmc_problem &p, const StepKey &k, int *kernel,
     // E6, against the fused design's default tile (64, 8, 16), 64^3 FP32 25
     // against 120, 128^3 FP32 192 against 203, FP16 101 against 133,
     // 160 x 150 x 155 FP32 345 against 591.  The autotuner may pick a fused one
-    // (128^3 FP32 with (128, 4, 16): 181).  The allocation-free step's field is
-    // one array per GPU: there AUTO takes the fused design at tau != 1, which
-    // needs no field, so that calls on several streams share no memory.
+    // (128^3 FP32 with (128, 4, 16): 181).  Batches, two passes on records chunk by
+    // chunk against fused: twelve members of 16^3 E6 FP32 11 against 83, of 48^3 to
+    // 88^3 376 against 567; where the fused tiles fit the members exactly, 24 of
+    // 64^3 E6 FP16 351 against 367, E4 with psi FP32 593 against 594, BF16 432
+    // against 422, two of 128^3 E4 with psi FP32 390 against 430.  The
+    // allocation-free step's field is one array per GPU: there AUTO takes the
+    // fused design at tau != 1, which needs no field, so that calls on several
+    // streams share no memory.
     if (k.node || p.kernel == SCMC_KERNEL_TWO_PASS || p.kernel == SCMC_KERNEL_TWO_PASS_MOM ||
         (p.kernel == SCMC_KERNEL_AUTO && t[0] == 0 && (own_field || k.mom)) ||
         (p.kernel == SCMC_KERNEL_AUTO && p.rounding == SCMC_ROUND_STOCHASTIC)) {
@@ -1787,16 +1792,18 @@ static int batch_tiles(const std::vector<scmc_problem> &ps, int kernel,
 // launch between pass 2 of one chunk and pass 1 of the next measured no
 // faster.)  A chunk of one member runs the single-lattice kernels with that
 // member's description as an argument (no per-block tile and member loads).
-// The fused designs (one persistent launch), the density two-pass and
+// The any-tau two passes run by the same chunks: 24 members of 64^3 E4 with psi,
+// us per step over the whole list and by chunks, FP32 632, 593, BF16 478, 432.
+// The fused designs (one persistent launch), two dimensions at tau != 1 and
 // stochastic rounding (whose step counter advances at the first tile of
-// pass 1) run pass 1 and then pass 2 over the whole list.
+// pass 1) run the whole list at once.
 static void batch_set_ops(scmc_batch *b) {
     const Common &c = b->c;
     b->ops.clear();
     b->groups.clear();
     if (c.kernel == SCMC_KERNEL_FUSED) return;
     std::vector<std::vector<int>> members_of;  // by chunk
-    bool chunked = c.key.mom;
+    bool chunked = c.key.mom || c.key.dim == 3;
     for (const Lat &L : b->lats) chunked = chunked && !L.m.sr;
     std::vector<BatchOp> ops;
     if (chunked) {
@@ -1856,7 +1863,7 @@ static void batch_set_ops(scmc_batch *b) {
         }
         // a chunk of more than MOM_LIST members: full launches first (129 of 24^3:
         // 64, 64 and 1 fill 256 CUs in one round each, 43 three times in two)
-        g.mom = true;
+        g.mom = c.key.mom;
         for (size_t m0 = 0; m0 < ms.size() && g.mom; m0 += MOM_LIST) {
             const size_t m1 = std::min(ms.size(), m0 + MOM_LIST);
             BatchGroup::Launch launch;
