@@ -117,7 +117,7 @@ __device__ __forceinline__ void fused_collide(
     R nA, nB, FA[3], FB[3];
     lds_force<TX, TY, ORDER, R, PSI>(m, lds, k, tx, ty, nA, nB, FA, FB);
     const int voff = (((zc * m.ny) + (y0 + ty)) * m.nx + (x0 + tx)) * (int)sizeof(T);
-    site_collide<3, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R) {
+    site_collide<3, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v) {
         RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), dst.r[J], voff,
                             i * dst.plane_bytes);
     });
@@ -134,7 +134,7 @@ __device__ __forceinline__ void fused_collide_mom(
     R nA, nB, FA[3], FB[3];
     lds_force<TX, TY, ORDER, R, PSI>(m, lds, k, tx, ty, nA, nB, FA, FB);
     const int voff = (((zc * m.ny) + (y0 + ty)) * m.nx + (x0 + tx)) * (int)sizeof(T);
-    collide_tau1<3, R>(m, mom, FA, FB, [&](int J, int i, R v, R) {
+    collide_tau1<3, R>(mom, FA, FB, [&](int J, int i, R v) {
         RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), dst.r[J], voff,
                             i * dst.plane_bytes);
     });

@@ -133,8 +133,8 @@ template <int D, int ORDER> struct Stencil {
 
 // ----------------------------------------------------------- storage formats
 // encode(v, w, n0) and decode(h, w, n0) convert a population; w_i n0_J is the
-// offset reference (used by the FP16 / BF16 offset formats only).  to_raw_sr
-// rounds stochastically, against ref = w_i n0_J.  The two-pass kernels store
+// offset reference (used by the FP16 / BF16 offset formats only).  encode_sr
+// rounds stochastically.  The two-pass kernels store
 // non-temporally: every population is written once per step and only read
 // again by the next step, after the whole buffer has streamed.
 struct StoreF64 {
@@ -144,7 +144,7 @@ struct StoreF64 {
     __device__ __forceinline__ static T encode(R v, R, R) { return v; }
     __device__ __forceinline__ static R decode(T v, R, R) { return v; }
     __device__ __forceinline__ static R stored(R v, R, R) { return v; }
-    __device__ __forceinline__ static T to_raw_sr(R v, R, unsigned) { return v; }
+    __device__ __forceinline__ static T encode_sr(R v, R, R, unsigned) { return v; }
 };
 
 struct StoreF32 {
@@ -154,7 +154,7 @@ struct StoreF32 {
     __device__ __forceinline__ static T encode(R v, R, R) { return v; }
     __device__ __forceinline__ static R decode(T v, R, R) { return v; }
     __device__ __forceinline__ static R stored(R v, R, R) { return v; }
-    __device__ __forceinline__ static T to_raw_sr(R v, R, unsigned) { return v; }
+    __device__ __forceinline__ static T encode_sr(R v, R, R, unsigned) { return v; }
 };
 
 struct StoreF16 {
@@ -187,8 +187,8 @@ struct StoreF16 {
     // Stochastic rounding: 13 random bits added below the half's last
     // mantissa bit, then truncation.  Half subnormals (|h| < 2^-14) are
     // rounded to nearest, their absolute error being below 2^-25.
-    __device__ __forceinline__ static T to_raw_sr(R v, R ref, unsigned r) {
-        const float x = v - ref;
+    __device__ __forceinline__ static T encode_sr(R v, R w, R n0, unsigned r) {
+        const float x = __builtin_fmaf(-w, n0, v);  // as encode: what decode adds
         if (!(fabsf(x) >= 6.103515625e-05f) || fabsf(x) > 6.5e4f)
             return __half_as_ushort(__float2half_rn(x));
         const unsigned u = __float_as_uint(x) + (r & 0x1FFFu);
@@ -241,8 +241,8 @@ struct StoreBF16 {
     // Stochastic rounding: 16 random bits added below the kept half of the
     // binary32 pattern, then truncation (sign-magnitude: unbiased for both
     // signs); infinities and NaN go the nearest-even way.
-    __device__ __forceinline__ static T to_raw_sr(R v, R ref, unsigned r) {
-        const float x = v - ref;
+    __device__ __forceinline__ static T encode_sr(R v, R w, R n0, unsigned r) {
+        const float x = __builtin_fmaf(-w, n0, v);  // as encode: what decode adds
         const uint32_t u = __float_as_uint(x);
         if ((u & 0x7f800000u) == 0x7f800000u) return f32_to_bf16_dev(x);
         return (uint16_t)((u + (r & 0xFFFFu)) >> 16);

@@ -336,7 +336,7 @@ __device__ __forceinline__ void collide_component(const R (&f)[Lattice<D>::Q], d
 }
 
 // Common velocity and collision of both components; every f*_i^J is handed to
-// sink(J, i, value, w_i n0_J) as soon as it is formed.
+// sink(J, i, value) as soon as it is formed.
 template <int D, class R, class Sink>
 __device__ __forceinline__ void site_collide(const Member &m,
                                              const R (&f)[2][Lattice<D>::Q],
@@ -365,12 +365,11 @@ __device__ __forceinline__ void site_collide(const Member &m,
                 p[k] = oA * fma_r(R(0.5), FA[k], (R)j[0][k]) + oB * fma_r(R(0.5), FB[k], (R)j[1][k]);
         }
     }
-    const R n0[2] = {(R)m.n0[0], (R)m.n0[1]};
 #pragma unroll
     for (int J = 0; J < 2; ++J)
         collide_component<D, R>(f[J], nx[J], J == 0 ? nA : nB, J == 0 ? FA : FB, p, inv,
                                 J == 0 ? oA : oB,
-                                [&](int i, R v) { sink(J, i, v, (R)L::W[i] * n0[J]); });
+                                [&](int i, R v) { sink(J, i, v); });
 }
 
 // Moments that the collision needs at omega = 1: n_J and the total momentum
@@ -494,16 +493,13 @@ __device__ __forceinline__ void collide_tau1_emit(const R (&mom)[NMOM], const R 
                                      [&](int i, R v) { return emit(J, i, v); });
 }
 
-// The same with every f*_i^J handed to sink(J, i, value, w_i n0_J), the
+// The same with every f*_i^J handed to sink(J, i, value), the
 // closure taken on the values as formed.
 template <int D, class R, class Sink>
-__device__ __forceinline__ void collide_tau1(const Member &m, const R (&mom)[NMOM],
-                                             const R (&FA)[3], const R (&FB)[3],
-                                             Sink &&sink) {
-    using L = Lattice<D>;
-    const R n0[2] = {(R)m.n0[0], (R)m.n0[1]};
+__device__ __forceinline__ void collide_tau1(const R (&mom)[NMOM], const R (&FA)[3],
+                                             const R (&FB)[3], Sink &&sink) {
     collide_tau1_emit<D, R>(mom, FA, FB, [&](int J, int i, R v) {
-        sink(J, i, v, (R)L::W[i] * n0[J]);
+        sink(J, i, v);
         return v;
     });
 }
@@ -558,13 +554,14 @@ __device__ __forceinline__ void site_collide_store(
     typename ST::T *base = dst + m.pop_off;
     if (m.sr) {
         SiteRng rng(m.seed, *m.step_ctr, (unsigned)(m.pop_off + s));
-        site_collide<D, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R ref) {
-            __builtin_nontemporal_store(ST::to_raw_sr(v, ref, rng.next()),
-                                        base + (long)(J * Lattice<D>::Q + i) * m.N + s);
+        site_collide<D, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v) {
+            __builtin_nontemporal_store(
+                ST::encode_sr(v, (R)Lattice<D>::W[i], (R)m.n0[J], rng.next()),
+                base + (long)(J * Lattice<D>::Q + i) * m.N + s);
         });
         return;
     }
-    site_collide<D, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R) {
+    site_collide<D, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v) {
         __builtin_nontemporal_store(ST::encode(v, (R)Lattice<D>::W[i], (R)m.n0[J]),
                                     base + (long)(J * Lattice<D>::Q + i) * m.N + s);
     });

@@ -185,7 +185,7 @@ __device__ __forceinline__ void collide_site(const Member &m, const typename ST:
         site_force_fn<3, ORDER, PSI, R, 4 * kRecord<PSI>, true>(m, x, y, z, nA, nB, FA, FB, fetch);
         const PopBuf<ST> db = make_popbuf<ST, 19>(dst, m);
         const int voff = s * (int)sizeof(T);
-        site_collide<3, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v, R) {
+        site_collide<3, R>(m, f, nA, nB, FA, FB, [&](int J, int i, R v) {
             RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), db.r[J], voff,
                                 i * db.plane_bytes);
         });
@@ -256,13 +256,14 @@ __device__ __forceinline__ void collide_mom_site(const Member &m,
     typename ST::T *out = dst + m.pop_off;
     if (m.sr) {
         SiteRng rng(m.seed, *m.step_ctr, (unsigned)(m.pop_off + s));
-        collide_tau1<D, R>(m, mm, FA, FB, [&](int J, int i, R v, R ref) {
-            __builtin_nontemporal_store(ST::to_raw_sr(v, ref, rng.next()),
-                                        out + (long)(J * Lattice<D>::Q + i) * m.N + s);
+        collide_tau1<D, R>(mm, FA, FB, [&](int J, int i, R v) {
+            __builtin_nontemporal_store(
+                ST::encode_sr(v, (R)Lattice<D>::W[i], (R)m.n0[J], rng.next()),
+                out + (long)(J * Lattice<D>::Q + i) * m.N + s);
         });
         return;
     }
-    collide_tau1<D, R>(m, mm, FA, FB, [&](int J, int i, R v, R) {
+    collide_tau1<D, R>(mm, FA, FB, [&](int J, int i, R v) {
         __builtin_nontemporal_store(ST::encode(v, (R)Lattice<D>::W[i], (R)m.n0[J]),
                                     out + (long)(J * Lattice<D>::Q + i) * m.N + s);
     });
@@ -348,13 +349,14 @@ __device__ __forceinline__ void collide_mom_site_buf(const Member &m, const PopB
     }
     if constexpr (SR) {
         SiteRng rng(m.seed, *m.step_ctr, (unsigned)(m.pop_off + s));
-        collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R ref) {
-            RawBuf<T>::store_nt(ST::to_raw_sr(v, ref, rng.next()), db.r[J], voff,
-                                i * db.plane_bytes);
+        collide_tau1<3, R>(mm, FA, FB, [&](int J, int i, R v) {
+            RawBuf<T>::store_nt(
+                ST::encode_sr(v, (R)Lattice<3>::W[i], (R)m.n0[J], rng.next()), db.r[J], voff,
+                i * db.plane_bytes);
         });
         return;
     }
-    collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R) {
+    collide_tau1<3, R>(mm, FA, FB, [&](int J, int i, R v) {
         RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), db.r[J], voff,
                             i * db.plane_bytes);
     });
@@ -426,12 +428,13 @@ __global__ void __launch_bounds__(TX *TY)
                 m.rest[s] = r;
             } else if constexpr (SR) {
                 SiteRng rng(m.seed, *m.step_ctr, (unsigned)(m.pop_off + s));
-                collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R ref) {
-                    RawBuf<T>::store_nt(ST::to_raw_sr(v, ref, rng.next()), db.r[J], voff,
-                                        i * db.plane_bytes);
+                collide_tau1<3, R>(mm, FA, FB, [&](int J, int i, R v) {
+                    RawBuf<T>::store_nt(
+                        ST::encode_sr(v, (R)Lattice<3>::W[i], (R)m.n0[J], rng.next()), db.r[J], voff,
+                        i * db.plane_bytes);
                 });
             } else {
-                collide_tau1<3, R>(m, mm, FA, FB, [&](int J, int i, R v, R) {
+                collide_tau1<3, R>(mm, FA, FB, [&](int J, int i, R v) {
                     RawBuf<T>::store_nt(ST::encode(v, (R)Lattice<3>::W[i], (R)m.n0[J]), db.r[J],
                                         voff, i * db.plane_bytes);
                 });
