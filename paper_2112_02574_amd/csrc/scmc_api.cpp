@@ -2119,8 +2119,9 @@ struct Candidate {
 // Designs this problem can run: for kernel AUTO the population-ring fused
 // designs (plain and pipelined) over the compiled tiles and three z-chunk
 // lengths and, at tau = 1, the moment-ring fused designs and the moment
-// two-pass design, otherwise the any-tau two passes; for a fixed fused design,
-// its tiles only.
+// two-pass design, otherwise the any-tau two passes beside a fused design (by
+// themselves they leave nothing to choose); for a fixed fused design, its tiles
+// only.
 std::vector<Candidate> candidates(const scmc_problem &p, const StepKey &k0, int nx) {
     static const int tiles[][2] = {{64, 4}, {32, 8},  {64, 8}, {32, 16},
                                    {128, 4}, {128, 8}, {64, 16}};
@@ -2152,7 +2153,7 @@ std::vector<Candidate> candidates(const scmc_problem &p, const StepKey &k0, int 
                 if (fused_supported(k, c.tile)) out.push_back(c);
             }
         }
-    if (p.kernel == SCMC_KERNEL_AUTO && !tau1 && k0.dim == 3)
+    if (p.kernel == SCMC_KERNEL_AUTO && !tau1 && !out.empty())
         out.push_back(Candidate{SCMC_KERNEL_TWO_PASS, 0, 0, {0, 0, 0}});
     if (p.kernel == SCMC_KERNEL_AUTO && tau1) {
         out.push_back(Candidate{SCMC_KERNEL_TWO_PASS, 0, 1, {0, 0, 0}});
