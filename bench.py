@@ -14,12 +14,13 @@ multiple of 2^11 (Sec. 4), inside the timed region when that falls there, and
 once after it for the reported observables otherwise.
 
 Prints one JSON line: MLUPS (million lattice-site updates per second, both
-components), the roofline of the step kernels (the bytes a step moves over the
-event-timed kernel time, against the 8 TB/s HBM peak; the moment design moves
-24 B of moments per site each way in FP32 and the populations, 304 B, once per
-block of steps, and is bound by its vector instructions instead), the HBM
-traffic measured by rocprofv3 counters for the same kernel source when
-available, and the FP64 CPU oracle timed on a bounded sample of the same
+components), the roofline of the step kernels (the vector instructions of the
+moment design in blocks of steps, counted by rocprofv3 for the same kernel
+source, over the event-timed kernel time against one per SIMD and 4 cycles; of
+the other designs, and beside it, the bytes a step moves against the 8 TB/s HBM
+peak; the moment design moves 24 B of moments per site each way in FP32 and the
+populations, 304 B, once per block), the HBM traffic measured by the counters
+when available, and the FP64 CPU oracle timed on a bounded sample of the same
 workload.  Beside it go the step rates of the other
 storage formats (FP64, FP16 and BF16 offsets) on the same droplet and of the
 48-member batched sweep (in 64-step graphs), each over a short timed run.
@@ -40,6 +41,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+# vector instructions of 64 lanes: 256 CUs x 4 SIMDs, one per 4 cycles each at 2.4 GHz
+VALU_PEAK_G = 256 * 4 * 2.4 / 4
 KERNELS = {"auto": 0, "two_pass": 1, "fused": 2, "fused_repull": 3, "fused_pipe": 4,
            "fused_mom": 5, "fused_mom_pipe": 6, "two_pass_mom": 7}
 KERNEL_NAMES = {v: k for k, v in KERNELS.items()}
@@ -58,6 +61,8 @@ PROFILE_RUNS = {"f32": "--storage f32 --kernel two_pass_mom",
                 "f16_node": "--storage f16_node --kernel two_pass_mom --tile 64 8 8",
                 "bf16_node": "--storage bf16_node --kernel two_pass_mom --tile 64 8 8",
                 "batch48": "--batch-only"}
+SQ_COUNTERS = ("SQ_WAVES SQ_INSTS_VALU SQ_INSTS_LDS SQ_INSTS_VMEM_RD SQ_INSTS_VMEM_WR "
+               "SQ_INSTS_SALU SQ_WAVE_CYCLES SQ_BUSY_CYCLES")
 
 
 def profile_commands(tag):
@@ -72,6 +77,8 @@ def profile_commands(tag):
                  f"-- python3 bench.py --steps 20 --warmup 5 --cpu-steps 0 --variant-steps 0 --init tanh {run}",
         "write": f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d gpurun_out/prof{sub}_write -o write "
                  f"-- python3 bench.py --steps 20 --warmup 5 --cpu-steps 0 --variant-steps 0 --init tanh {run}",
+        "sq": f"rocprofv3 --pmc {SQ_COUNTERS} --output-format csv -d gpurun_out/prof{sub}_sq -o sq "
+              f"-- python3 bench.py --steps 20 --warmup 5 --cpu-steps 0 --variant-steps 0 --init tanh {run}",
         "copy_fetch": "rocprofv3 --pmc FETCH_SIZE --output-format csv -d gpurun_out/prof_copy_fetch "
                       "-o cfetch -- python3 bench.py --copy-calib 1024",
         "copy_write": "rocprofv3 --pmc WRITE_SIZE --output-format csv -d gpurun_out/prof_copy_write "
@@ -101,9 +108,9 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
-def measured_traffic(n_sites):
-    """HBM bytes per step from the committed rocprofv3 counter summary,
-    or None when it is missing or was taken on a different kernel source."""
+def measured(n_sites, what):
+    """A per-step figure of the committed rocprofv3 counter summary, or None
+    when it is missing or was taken on a different kernel source."""
     try:
         with open(TRAFFIC_JSON) as fh:
             t = json.load(fh)
@@ -111,7 +118,7 @@ def measured_traffic(n_sites):
         return None
     if t.get("kernel_source_hash") != kernel_source_hash() or t.get("sites") != n_sites:
         return None
-    return t.get("hbm_bytes_per_step")
+    return t.get(what)
 
 
 def _finite(v):
@@ -149,9 +156,9 @@ def summarize_profiles(outdir, tag="f32", L=128):
         name = [f for f in os.listdir(d) if f.endswith(suffix)][0]
         return list(csv.DictReader(open(os.path.join(d, name))))
 
-    def mean_counter(sub, prefix):
+    def mean_counter(sub, prefix, counter=None):
         v = [float(r["Counter_Value"]) for r in rows(sub, "_counter_collection.csv")
-             if r["Kernel_Name"].startswith(prefix)]
+             if r["Kernel_Name"].startswith(prefix) and counter in (None, r["Counter_Name"])]
         return sum(v) / len(v), len(v)
 
     stats = rows(f"prof{sub}_trace", "_kernel_stats.csv")
@@ -191,6 +198,11 @@ def summarize_profiles(outdir, tag="f32", L=128):
         # the counter runs take 5 + 20 steps (the batch's 1 + 20 + 20)
         n = 41 if tag == "batch48" else 25
         fetch, write, nf, nw = fetch + f * a / n, write + w * b / n, nf + a, nw + b
+    valu = {}  # vector instructions of a launch, by kernel
+    if os.path.isdir(os.path.join(outdir, f"prof{sub}_sq")):
+        for nm in names:
+            short = re.search(r"scmc::(\w+)", nm).group(1)
+            valu[short] = round(mean_counter(f"prof{sub}_sq", nm, "SQ_INSTS_VALU")[0])
     cf, _ = mean_counter("prof_copy_fetch", "__amd_rocclr_copyBuffer")
     cw, _ = mean_counter("prof_copy_write", "__amd_rocclr_copyBuffer")
     copy_bytes = 1024 * (1 << 20)
@@ -221,8 +233,9 @@ def summarize_profiles(outdir, tag="f32", L=128):
                                     "write_scale": round(sw, 4)},
                "hbm_bytes_per_step": round(hbm), "population_bytes_per_step": bps * N,
                "ratio_to_populations": round(hbm / (bps * N), 4),
+               "vector_instructions_per_launch": valu,
                "kernel_source_hash": kernel_source_hash(),
-               "commands": [cmds[k] for k in ("fetch", "write", "copy_fetch", "copy_write")]}
+               "commands": [cmds[k] for k in ("fetch", "write", "sq", "copy_fetch", "copy_write")]}
     with open(traffic_json, "w") as fh:
         json.dump(traffic, fh, indent=1)
         fh.write("\n")
@@ -251,8 +264,6 @@ DESIGN_RUNS = {"two_pass_mom": "--storage f32 --kernel two_pass_mom",
                "two_pass_mom_lds": "--storage f32 --kernel two_pass_mom --tile 64 8 8",
                "fused_mom": "--storage f32 --kernel fused_mom --tile 128 4 16",
                "two_pass": "--storage f32 --kernel two_pass"}
-SQ_COUNTERS = ("SQ_WAVES SQ_INSTS_VALU SQ_INSTS_LDS SQ_INSTS_VMEM_RD SQ_INSTS_VMEM_WR "
-               "SQ_INSTS_SALU SQ_WAVE_CYCLES SQ_BUSY_CYCLES")
 
 
 def design_profile_commands(name):
@@ -327,7 +338,7 @@ def summarize_designs(outdir, L=128):
                 q.get("SQ_INSTS_VMEM_RD", 0) / per, q.get("SQ_INSTS_VMEM_WR", 0) / per,
                 q.get("SQ_INSTS_SALU", 0) / per))
         summary.append((name, step_us, hbm, cmds))
-    lines += ["", "| design | us per step | MLUPS | % of 8 TB/s at 304 B/site | HBM bytes / algorithmic |",
+    lines += ["", "| design | us per step | MLUPS | populations of every step (304 B/site), % of 8 TB/s | HBM bytes / populations |",
               "|---|---|---|---|---|"]
     for name, us, hbm, _ in summary:
         lines.append("| %s | %.1f | %.0f | %.1f | %.3f |" % (
@@ -408,22 +419,33 @@ def _timed(step, steps, stream):
 STORAGE_BYTES = {"f64": 608, "f32": 304, "f16_offset": 152, "bf16_offset": 152,
                  "f16_node": 160, "bf16_node": 160}
 # bytes per site and step from moment field to moment field (D3Q19): n_A, n_B,
-# j and the remainders, read and written; node storage also its rest
-# populations
-MOMENT_BYTES = {"f64": 96, "f16_node": 64, "bf16_node": 64}
+# j and, but for FP64, the packed remainders, read and written
+MOMENT_BYTES = {"f64": 80}
 STEP_BLOCK = 64  # steps between one pass 1 and the next pass 2 in a long call
 PRECISION_JSON = os.path.join(ROOT, "profiles", "precision_256cube_asym.json")
 
 
 def moved_bytes(name, kernel, steps, graph=0):
     """Bytes per site that one step of a call of ``steps`` steps moves, averaged
-    over a block: the moment design reads the populations and writes moments
-    once, steps from moments to moments, and writes the populations once."""
+    over a block: the moment design reads the populations (node storage: with
+    the rest populations) and writes moments once, steps from moments to
+    moments, and writes the populations once."""
     pops = STORAGE_BYTES[name]
     if KERNEL_NAMES[kernel] != "two_pass_mom":
         return pops
     k, mom = min(graph or STEP_BLOCK, steps), MOMENT_BYTES.get(name, 48)
     return (pops + mom + (k - 1) * mom) / k
+
+
+def vector_instructions(n_sites, steps, graph=0):
+    """Vector instructions (of 64 lanes) of one step of such a call of the FP32
+    moment design, or None where they were not counted."""
+    per = measured(n_sites, "vector_instructions_per_launch") or {}
+    if "k_mom_step" not in per:
+        return None
+    k = min(graph or STEP_BLOCK, steps)
+    passes = sum(v for name, v in per.items() if name != "k_mom_step")
+    return (passes + (k - 1) * per["k_mom_step"]) / k
 
 
 def _storage_kinds(scmc):
@@ -607,7 +629,20 @@ def run(args):
     kernel_ms = step_ms / args.steps
     bps = moved_bytes(args.storage, kernel, min(args.steps, OBS_EVERY), args.graph)
     achieved = bps * N / (kernel_ms * 1e-3) / 1e9
-    traffic = measured_traffic(N) if args.storage == "f32" else None
+    f32 = args.storage == "f32"
+    traffic = measured(N, "hbm_bytes_per_step") if f32 else None
+    block = min(args.steps, OBS_EVERY)
+    # in blocks the moment design is bound by the rate of vector instructions,
+    # every other design by the bytes that it moves
+    hbm = {"achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": round(achieved / HBM_PEAK_GBS, 4)}
+    roof = dict(bound="hbm", **hbm)
+    if KERNEL_NAMES[kernel] == "two_pass_mom" and block > 1:
+        instr = vector_instructions(N, block, args.graph) if f32 else None
+        rate = instr / (kernel_ms * 1e-3) / 1e9 if instr else None
+        roof = {"bound": "vector_instructions", "achieved": round(rate, 1) if rate else None,
+                "peak": round(VALU_PEAK_G, 1), "unit": "G wave instructions/s",
+                "frac": round(rate / VALU_PEAK_G, 4) if rate else None, "hbm": hbm}
     # the streaming half of the step without arithmetic, in the same buffers:
     # the bandwidth ceiling of any design that moves each population once per
     # step (it overwrites the state, so it runs after the observables)
@@ -635,10 +670,7 @@ def run(args):
                    # the per-site sums (n_J, momentum, force, the mass closure)
                    # accumulate FP32 values in FP64, order-free
                    "site_sums": "f64"},
-        "roofline": {"bound": "vector_instructions" if KERNEL_NAMES[kernel] == "two_pass_mom"
-                     and args.steps > 1 else "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "kernel_ms": round(kernel_ms, 5),
+        "roofline": {**roof, "traffic": traffic, "kernel_ms": round(kernel_ms, 5),
                      "bytes_per_site": round(bps, 1),
                      "pull_copy_GBs": round(copy_gbs, 1),
                      "pull_copy_frac": round(copy_gbs / HBM_PEAK_GBS, 4),

@@ -29,9 +29,13 @@
 //
 // us per step against pass 1 and pass 2 of every step: E6 128^3 FP32 122 ->
 // 64, 150 x 141 x 165 FP32 337 -> 120, 192^3 FP16 343 -> 236, 100 x 84 x 92
-// FP64 102 -> 37, E4 with psi 63^3 FP32 27.4 -> 17.8.  At 128^3 a lane issues
-// 325 vector instructions per plane (430 with 16 exchanged populations
-// instead of 12 sums), which keeps the SIMDs busy 86 % of the time.
+// FP64 102 -> 37, E4 with psi 63^3 FP32 27.4 -> 17.4.  At 128^3 a lane issues
+// 307 vector instructions per plane (430 with 16 exchanged populations
+// instead of 12 sums), which keeps the SIMDs busy 85 % of the time; at 63^3 72 %,
+// the rest of it waiting on the exchange.  FP64 with psi does not fit a lane's 128
+// registers (E6 spills 33 of them, E4 3): 48^3 E4 takes 15.5 us per step, with
+// psi = n 11.5, 40^3 E6 22.6, with psi = n 10.6 (step_rules.h keeps it off the
+// sizes where the two passes are faster).
 #pragma once
 
 #include "fused_impl.h"  // xcd_remap

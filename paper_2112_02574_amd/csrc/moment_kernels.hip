@@ -21,10 +21,15 @@ SCMC_MOM_COMBOS(SCMC_EXTERN)
 // planes a chunk marches (two more than it stores, and 1.5 for filling the
 // ring), times the time of a plane, 1.6 us + 0.06 us per wavefront: a
 // wavefront's latency and the vector instructions of all of them.  The model
-// orders measured shapes well (us per step, w x h x zc): 63^3 E4 FP32
-// 32x11x3 19.0, 13x21x5 22.7, 16x21x6 27.6, 13x13x8 24.1; 128^3 E6 FP32
-// 26x16x22 71, 32x13x13 (two rounds) 86, 19x16x32 80; 48^3 E6 FP32
-// 24x10x2 11.6, 24x16x4 18.5.  Both fields of a step lie in the caches up to
+// orders measured shapes (us per step of long calls, w x h x zc, the model's
+// choice first): 63^3 E4 FP32 21x16x3 13.9, 32x11x3 13.6, 13x21x5 16.5, 13x13x8
+// 17.6, 16x21x6 20.3, with psi 17.4, 17.2, 21.0; 128^3 E6 FP32 32x13x22 64.7,
+// 26x16x22 65.2, 32x13x26 74.4, 19x16x32 75.4, 32x13x13 (two rounds) 79.9; 48^3 E6
+// FP32 16x16x2 11.4, 24x10x2 11.0, 24x16x3 15.6, 24x16x4 18.2; 32^3 E4 FP32 8x16x1
+// 6.4, 32x8x1 7.6, 16x16x2 9.5.  Its times are those of psi = n without 16-bit
+// rounding, within about 10 % from 60^3 on (63^3 E4 15.6 against 13.9, 128^3 E6
+// 65.8 against 64.7) and high below (32^3 E4 8.9 against 6.4); psi adds 10 to 30 %,
+// FP64 E6 with psi doubles them.  Both fields of a step lie in the caches up to
 // about 170^3, and beyond that its 48 B per site still stream faster than it
 // computes.
 // The search below runs over columns for a given number of planes per chunk

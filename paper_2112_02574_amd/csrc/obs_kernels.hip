@@ -28,7 +28,9 @@ __device__ __forceinline__ void common_velocity(const Member &m, const double (&
 constexpr int OB_BX = 64, OB_BY = 4, OB_THREADS = OB_BX * OB_BY;
 
 // Population value as a double: the stored value plus, for the offset
-// formats, the same single-precision reference the step kernels add.
+// formats, the single-precision reference w_i n0 (as the host reads and writes
+// populations).  The step kernels add the product unrounded and round the sum
+// to single precision: the two differ by at most half a unit of each.
 template <class ST> struct Decode;
 template <> struct Decode<StoreF64> {
     __device__ static double get(const double *p, long i, double, double) {
