@@ -121,6 +121,10 @@ __global__ void __launch_bounds__(ONCE_THREADS)
 // their boxes fit: E6 with psi = n in FP64 (8^3 8.4, 9.2; 24^3 11.2, 11.4;
 // 16 x 32 x 32 10.7, 11.4) and what one workgroup of the two passes holds, 256
 // nodes, at E6 (5^3 5.9, 7.1).
+// In graphs, without the calls' own time, the sides lie as far apart (FP32 E6
+// 32^3 8.8, 12.1; FP16 E4 40^3 8.8, 9.8; FP64 E6 24^3 9.9, 11.5).  A Python loop
+// of scmc_step_static, 8.6 us a call with one launch, takes 11.3 with two whatever
+// they do, which hides the difference (FP32 E6 32^3 11.1, 12.5; FP16 11.3, 10.5).
 bool step_once_shape(const StepKey &k, const Member &m, MomShape *g) {
     if (k.dim != 3 || k.mom != 1 || k.node || k.sr || (k.order != 4 && k.order != 6)) return false;
     if (k.order == 6 && !k.psi && (k.storage == ST_F64 || m.N <= 256)) return false;
